@@ -135,29 +135,25 @@ void check_graphs(cube_batch& b) {
 
 // z layout of the solve: 1 allocates the scratch copy (one mesh-sized buffer) if needed, 0 keeps
 // any allocated scratch, -1 selects 0 and frees the scratch. The scratch also holds the move
-// passes' per (cell, displacement) counts and slots (27 x 4 bytes each per coarse cell, less than
-// the mesh's 64 x 4): the copy is live only inside a solve, the counts and slots only inside a
-// move, so one buffer serves both and their own allocation is given back.
+// passes' per (cell, displacement) counts (27 x 4 bytes per coarse cell, less than the mesh's
+// 64 x 4): the copy is live only inside a solve, the counts only inside a move, so one buffer serves
+// both and their own allocation is given back.
 void set_z_layout(Sim& s, int layout) {
   FFTPlan& pl = s.mesh_plan;
   s.config_gen++;
   const size_t mig_bytes = sizeof(uint32_t) * 27 * (size_t)s.nc3;
   if (layout == 1 && !pl.zscratch) {
     const size_t zb = pl.field_floats() * sizeof(float);
-    char* w = static_cast<char*>(s.dmalloc(std::max(zb, 2 * mig_bytes)));
+    char* w = static_cast<char*>(s.dmalloc(std::max(zb, mig_bytes)));
     s.dfree(s.mig);
-    s.dfree(s.slot);
     pl.zscratch = reinterpret_cast<float2*>(w);
     s.mig = reinterpret_cast<uint32_t*>(w);
-    s.slot = reinterpret_cast<uint32_t*>(w + mig_bytes);
   }
   if (layout < 0 && pl.zscratch) {
     uint32_t* m = static_cast<uint32_t*>(s.dmalloc(mig_bytes));
-    uint32_t* sl = static_cast<uint32_t*>(s.dmalloc(mig_bytes));
     s.dfree(pl.zscratch);
     pl.zscratch = nullptr;
     s.mig = m;
-    s.slot = sl;
   }
   pl.zlayout = layout > 0 ? 1 : 0;
 }

@@ -129,8 +129,7 @@ struct Sim {
 
   // move scratch
   float* vinv = nullptr;       // nc3 encode scale 1/(sigma sqrt(2/pi))
-  uint32_t* mig = nullptr;     // 27 x nc3 counts per (source cell, displacement)
-  uint32_t* slot = nullptr;    // 27 x nc3 prefix per (new cell, source offset)
+  uint32_t* mig = nullptr;     // 27 x nc3 counts per (displacement, source cell); the link turns them into slots
   int64_t* mom = nullptr;      // 4 x nc3: S1x, S1y, S1z, S2
   double* dev = nullptr;       // nc3 3-D velocity variance per cell
   uint64_t* blk_n = nullptr;   // per link block: count

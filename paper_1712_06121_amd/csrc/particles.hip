@@ -404,8 +404,7 @@ struct MoveArgs {
   const int16_t* tbucket;
   int nbucket;
   int vhalf;
-  uint32_t* mig;
-  const uint32_t* slot;
+  uint32_t* mig;  // per (displacement, source cell): counts after the count pass, slots after the link
   int64_t* mom;
   uint32_t* flags;
   // initial conditions
@@ -1012,7 +1011,8 @@ __device__ __forceinline__ void move_scatter_tile(MoveArgs a, const unsigned lb)
       const int nx = wrapi(g.cx0 + ox + m.k[0], a.nc), ny = wrapi(g.cy0 + oy + m.k[1], a.nc);
       const int nz = wrapi(g.cz0 + oz + m.k[2], a.nc);
       const int64_t cn = nx + (int64_t)a.nc * (ny + (int64_t)a.nc * nz);
-      const uint64_t dst = a.off_n[cn] + a.slot[(int64_t)(26 - dcode) * a.nc3 + cn] + gbase + (uint32_t)rin;
+      const int64_t co = (g.cx0 + ox) + (int64_t)a.nc * ((g.cy0 + oy) + (int64_t)a.nc * (g.cz0 + oz));
+      const uint64_t dst = a.off_n[cn] + a.mig[(int64_t)dcode * a.nc3 + co] + gbase + (uint32_t)rin;
       if (dst < (uint64_t)a.cap) {
         const float inv = a.vinv[cn];
 #pragma unroll
@@ -1368,7 +1368,8 @@ __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
         uint64_t dbase = 0;
         float inv = 0.0f, vcn[3] = {0.0f, 0.0f, 0.0f};
         if (active) {
-          dbase = a.off_n[cn] + a.slot[(int64_t)(26 - dcode) * a.nc3 + cn];
+          const int64_t co = (g.cx0 + ci) + (int64_t)a.nc * ((g.cy0 + o1) + (int64_t)a.nc * (g.cz0 + o2));
+          dbase = a.off_n[cn] + a.mig[(int64_t)dcode * a.nc3 + co];
           inv = a.vinv[cn];
 #pragma unroll
           for (int d = 0; d < 3; ++d) vcn[d] = a.vc_n[d * a.nc3 + cn];
@@ -1438,11 +1439,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
 
 // ---------------------------------------------------------------------------------------------
 // Link: per new cell, counts from the 27 source cells in offset order (z, y, x each -1, 0, +1),
-// the slot prefix per source offset, the mean velocity and the 3-D velocity variance.
+// the slot prefix per source offset, the mean velocity and the 3-D velocity variance. The entry
+// (displacement d, source cell) of the count table belongs to exactly one (new cell, source offset
+// 26 - d), so the slots overwrite the counts in place, one thread per new cell.
 // ---------------------------------------------------------------------------------------------
 struct LinkArgs {
-  const uint32_t* mig;
-  uint32_t* slot;
+  uint32_t* mig;
   uint32_t* cnt_n;
   int64_t* mom;
   float* vc_n;
@@ -1459,34 +1461,41 @@ struct LinkArgs {
 // of a link block cannot overflow; the sum over the blocks is exact in 128 bits (k_scan_blocks)
 constexpr double kDevTermLimit = 18014398509481984.0;  // 2^54
 
+// Bound by memory latency, then by its 27 words read and written per cell: the 27 counts and the
+// four moments of a cell are requested together (with one load waiting for the store before it, a
+// 16^3 box took 15 us, 128^3 cells 139 us). Cell indices fit 32 bits (nc <= 512), plane
+// bases are uniform.
 __device__ __forceinline__ void link_block(const LinkArgs& a, const unsigned blk) {
-  __shared__ unsigned long long sn[LINK_BLK];
-  __shared__ long long sq[LINK_BLK];
+  __shared__ unsigned long long sn[LINK_BLK / 64], sq[LINK_BLK / 64];
   if (workgroup_step_failed(a.flags)) return;
-  const int64_t c = (int64_t)blk * LINK_BLK + threadIdx.x;
+  const uint32_t c = blk * LINK_BLK + threadIdx.x, nc = (uint32_t)a.nc;
   uint32_t n = 0;
   long long q = 0;
-  if (c < a.nc3) {
+  if (c < (uint32_t)a.nc3) {
+    unsigned long long* const mom = reinterpret_cast<unsigned long long*>(a.mom);
+    const long long s1x = (long long)mom[c], s1y = (long long)(mom + a.nc3)[c], s1z = (long long)(mom + 2 * a.nc3)[c],
+                    s2 = (long long)(mom + 3 * a.nc3)[c];
     if (a.cnt_direct) {
       n = a.cnt_direct[c];
     } else {
-      const int x = (int)(c % a.nc), y = (int)((c / a.nc) % a.nc), z = (int)(c / ((int64_t)a.nc * a.nc));
-      uint32_t run = 0;
+      const uint32_t x = c % nc, y = (c / nc) % nc, z = c / (nc * nc);
+      const uint32_t xs[3] = {x ? x - 1 : nc - 1, x, x + 1 < nc ? x + 1 : 0};
+      const uint32_t ys[3] = {nc * (y ? y - 1 : nc - 1), nc * y, nc * (y + 1 < nc ? y + 1 : 0)};
+      const uint32_t zs[3] = {nc * nc * (z ? z - 1 : nc - 1), nc * nc * z, nc * nc * (z + 1 < nc ? z + 1 : 0)};
+      uint32_t m[27];
+#pragma unroll
+      for (int j = 0; j < 27; ++j) m[j] = (a.mig + (int64_t)(26 - j) * a.nc3)[xs[j % 3] + ys[(j / 3) % 3] + zs[j / 9]];
+#pragma unroll
       for (int j = 0; j < 27; ++j) {
-        const int ox = j % 3 - 1, oy = (j / 3) % 3 - 1, oz = j / 9 - 1;
-        const int64_t src = wrapi(x + ox, a.nc) + (int64_t)a.nc * (wrapi(y + oy, a.nc) + (int64_t)a.nc * wrapi(z + oz, a.nc));
-        const uint32_t mcount = a.mig[(int64_t)(26 - j) * a.nc3 + src];
-        a.slot[(int64_t)j * a.nc3 + c] = run;
-        run += mcount;
+        (a.mig + (int64_t)(26 - j) * a.nc3)[xs[j % 3] + ys[(j / 3) % 3] + zs[j / 9]] = n;
+        n += m[j];
       }
-      n = run;
     }
     a.cnt_n[c] = n;
-    const long long s1x = a.mom[c], s1y = a.mom[a.nc3 + c], s1z = a.mom[2 * a.nc3 + c], s2 = a.mom[3 * a.nc3 + c];
-    a.mom[c] = 0;
-    a.mom[a.nc3 + c] = 0;
-    a.mom[2 * a.nc3 + c] = 0;
-    a.mom[3 * a.nc3 + c] = 0;
+    mom[c] = 0;
+    (mom + a.nc3)[c] = 0;
+    (mom + 2 * a.nc3)[c] = 0;
+    (mom + 3 * a.nc3)[c] = 0;
     double m0 = 0.0, m1 = 0.0, m2 = 0.0, dev = 0.0;
     const double nd = (double)n;
     if (n > 0) {
@@ -1503,8 +1512,8 @@ __device__ __forceinline__ void link_block(const LinkArgs& a, const unsigned blk
       if (!(dev > 0.0)) dev = 0.0;
     }
     a.vc_n[c] = (float)m0;
-    a.vc_n[a.nc3 + c] = (float)m1;
-    a.vc_n[2 * a.nc3 + c] = (float)m2;
+    (a.vc_n + a.nc3)[c] = (float)m1;
+    (a.vc_n + 2 * a.nc3)[c] = (float)m2;
     a.dev[c] = dev;
     const double term = (dev * nd) * 1048576.0;
     if (term < kDevTermLimit) {
@@ -1514,19 +1523,21 @@ __device__ __forceinline__ void link_block(const LinkArgs& a, const unsigned blk
       q = 0;
     }
   }
-  sn[threadIdx.x] = n;
-  sq[threadIdx.x] = q;
-  __syncthreads();
-  for (int s = LINK_BLK / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) {
-      sn[threadIdx.x] += sn[threadIdx.x + s];
-      sq[threadIdx.x] += sq[threadIdx.x + s];
-    }
-    __syncthreads();
+  const unsigned long long wn = wave_sum_u64(n), wq = wave_sum_u64((unsigned long long)q);
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) {
+    sn[wave] = wn;
+    sq[wave] = wq;
   }
+  __syncthreads();
   if (threadIdx.x == 0) {
-    a.blk_n[blk] = sn[0];
-    a.blk_q[blk] = sq[0];
+    unsigned long long tn = 0, tq = 0;
+    for (int w = 0; w < LINK_BLK / 64; ++w) {
+      tn += sn[w];
+      tq += sq[w];
+    }
+    a.blk_n[blk] = tn;
+    a.blk_q[blk] = (int64_t)tq;
   }
 }
 
@@ -1839,7 +1850,6 @@ void launch_deposit(Sim& s, hipStream_t st) {
 static LinkArgs link_args(const Sim& s, int nxt, const uint32_t* cnt_direct) {
   LinkArgs l;
   l.mig = s.mig;
-  l.slot = s.slot;
   l.cnt_n = s.cnt[nxt];
   l.mom = s.mom;
   l.vc_n = s.vc[nxt];
@@ -1937,7 +1947,6 @@ static MoveArgs move_args(const Sim& s, int cur, float kfac, float dfac, bool de
   a.nbucket = s.nbucket;
   a.vhalf = (s.vm - 1) / 2;
   a.mig = s.mig;
-  a.slot = s.slot;
   a.mom = s.mom;
   a.flags = s.flags;
   a.kd = dev_sched ? s.sched_dev : nullptr;
