@@ -152,7 +152,9 @@ int cube_debug_inject_flag(cube_sim* sim, int32_t step, uint32_t flag);
  * each chunk waiting (polling an LDS word) until the previous one is ranked; after `polls` polls
  * (default 2^22, far beyond any legitimate wait) a chunk stops waiting and raises the count error
  * (8), so the step fails with CUBE_E_STATE and is not applied. A small value forces that path.
- * Errors: CUBE_E_INVALID (polls 0). */
+ * Steps normally place the records their count pass wrote (where there is device memory for them);
+ * a limit other than the default makes them recompute the move in the scatter of move_variant, with
+ * the same results. Errors: CUBE_E_INVALID (polls 0). */
 int cube_debug_set_turn_limit(cube_sim* sim, uint32_t polls);
 
 /* Adaptive time steps (Sec. 2.3.3: the step is bounded by the particles' largest velocity and

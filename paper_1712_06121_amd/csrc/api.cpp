@@ -17,16 +17,22 @@ namespace cube {
 void* Sim::dmalloc(size_t bytes) {
   void* p = nullptr;
   if (bytes == 0) bytes = 256;
-  if (has_alloc) {
-    p = alloc.alloc(bytes, alloc.user);
-    if (!p) throw Error{CUBE_E_NOMEM, "device allocator returned NULL for " + std::to_string(bytes) + " bytes"};
-  } else {
-    hipError_t e = hipMalloc(&p, bytes);
-    if (e != hipSuccess) {
+  auto try_alloc = [&]() {
+    if (has_alloc) {
+      p = alloc.alloc(bytes, alloc.user);
+    } else if (hipMalloc(&p, bytes) != hipSuccess) {
       (void)hipGetLastError();
-      throw Error{CUBE_E_NOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed"};
+      p = nullptr;
     }
+  };
+  try_alloc();
+  if (!p && rec) {  // the records only save time: they make room for what is needed
+    release_records(*this);
+    try_alloc();
   }
+  if (!p)
+    throw Error{CUBE_E_NOMEM, (has_alloc ? "device allocator returned NULL for " : "hipMalloc failed for ") +
+                                  std::to_string(bytes) + " bytes"};
   dev_bytes += (int64_t)bytes;
   owned.push_back(p);
   sizes.push_back(bytes);
@@ -49,7 +55,41 @@ void Sim::dfree(void* p) {
 
 // helpers shared with batch.cpp (declared in cube_internal.h)
 
+// The records take room that the simulation could do without, so they are allocated only where as
+// much again stays free on the device (2048^3 particles recompute the move instead), or, for jobs
+// of a server, whose admission counts footprints, within the job's own footprint (its
+// initial-condition fields are gone by then). Indices of places are 32-bit: below 2^31 particles.
+void ensure_records(Sim& s) {
+  if (s.rec || s.capacity >= ((int64_t)1 << 31)) return;
+  const size_t need = (size_t)s.capacity * (s.nchi == 1 ? 16 : 20);
+  if (need == 0) return;
+  if (s.rec_in_footprint) {
+    if (s.dev_bytes + (int64_t)need > footprint_bytes(s.p)) return;
+  } else {
+    size_t avail = 0, total = 0;
+    if (hipMemGetInfo(&avail, &total) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    if (avail / 2 < need) return;
+  }
+  try {
+    s.rec = static_cast<char*>(s.dmalloc(need));
+  } catch (const Error& e) {
+    if (e.code != CUBE_E_NOMEM) throw;
+    return;
+  }
+  s.config_gen++;  // captured step graphs hold the other scatter
+}
 
+void release_records(Sim& s) {
+  if (!s.rec) return;
+  if (s.stream) (void)hipStreamSynchronize(s.stream);
+  else (void)hipDeviceSynchronize();
+  s.dfree(s.rec);
+  s.rec = nullptr;
+  s.config_gen++;
+}
 
 void build_tables(Sim& s) {
   const int m = (1 << (8 * s.nnu)) - 1;
@@ -163,6 +203,7 @@ void read_maxima(Sim& s, double* vmax, double* gmax) {
 
 int enqueue_adaptive(Sim& s, int k) {
   const double af = s.p.a_final;
+  if (k > 0) ensure_records(s);
   for (int i = 0; i < k; ++i) {
     if (!s.half_drift_done) {
       const double v0 = std::sqrt((double)launch_state_speed2(s, s.stream));
@@ -340,6 +381,7 @@ int enqueue_steps(Sim& s, int k) {
     for (double& t : s.timings) t = 0.0;
     s.timing_calls = 0;
   }
+  if (k > 0 && s.steps_done < s.p.n_steps) ensure_records(s);
   for (int i = 0; i < k; ++i) {
     if (s.steps_done >= s.p.n_steps) {
       rc = CUBE_DONE;
@@ -549,6 +591,7 @@ int cube_init_ic(cube_sim* sim) {
     std::vector<void*> temps;
     float* psi[3];
     float* wk = nullptr;
+    cube::release_records(s);  // the displacement fields take their room
     cube::ic_fields(s, psi, &wk, temps, true);
     s.n = (int64_t)s.np * s.np * s.np;
     if (s.n > s.capacity) throw Error{CUBE_E_CAPACITY, "np_side^3 exceeds the capacity"};
@@ -736,6 +779,7 @@ int cube_stage_move(cube_sim* sim, float kfac, float dfac) {
   CUBE_GUARD(sim, {
     cube::require_particles(sim->s);
     const int cur0 = sim->s.cur;
+    cube::ensure_records(sim->s);
     cube::launch_move(sim->s, 0, kfac, dfac, nullptr, 0.0f, sim->s.stream, nullptr);
     CUBE_HIP(hipStreamSynchronize(sim->s.stream));
     try {

@@ -251,6 +251,7 @@ void autotune_sim(Sim& s) {
   solve_potential(s, s.stream);
   // move passes: per-corner gradient vs precomputed gradient tile, each pass timed on its own
   // (events around the count and the scatter pass), with this step's factors
+  ensure_records(s);
   const int j = std::min(s.steps_done, s.p.n_steps - 1);
   const float kf = (float)(-s.kicks[j] / 12.0), df = (float)s.drifts[j];
   float tc[2] = {0.f, 0.f}, ts[2] = {0.f, 0.f};
@@ -489,6 +490,8 @@ int cube_batch_step(cube_batch* b, int32_t k) {
     for (cube::Sim* s : ss)
       if (s->steps_done != done || s->cur != ss[0]->cur)
         throw Error{CUBE_E_STATE, "boxes of a batch must be at the same step (step them with cube_batch_step only)"};
+    if (k > 0 && done < ss[0]->p.n_steps)
+      for (cube::Sim* s : ss) cube::ensure_records(*s);
     // the initial half drift (no force) of every box, each on its own stream
     for (size_t i = 0; i < ss.size(); ++i) {
       cube::Sim& s = *ss[i];

@@ -95,6 +95,8 @@ struct CoarseTerm {
   const float2* inv_b = nullptr;  // 1 / B(f) for the signed coarse frequencies f + N_c/2, |f| < N_c/2
 };
 
+constexpr uint32_t kTurnLimit = 1u << 22;  // default poll limit of the gradient-tile scatter's ordered wait
+
 // ---- simulation ------------------------------------------------------------------------------
 struct Sim {
   cube_params p{};
@@ -193,7 +195,13 @@ struct Sim {
   uint32_t inject_flag = 0;
   // polls of the gradient-tile scatter's ordered section before a chunk gives up waiting and
   // raises the count error (tests of that path set it small)
-  uint32_t turn_limit = 1u << 22;
+  uint32_t turn_limit = kTurnLimit;
+
+  // Moved-particle records (16 bytes per particle of capacity, 20 with 2-byte positions) from the
+  // count pass to the scatter of a step; null when they are not used (ensure_records). Given back
+  // when another allocation needs the room.
+  char* rec = nullptr;
+  bool rec_in_footprint = false;  // only while the simulation stays within its cube_footprint (server jobs)
 
   // profiling: per-kernel event pairs recorded on the simulation's stream
   bool profiling = false;
@@ -215,6 +223,10 @@ float gconst(const Sim& s);       // Green's constant -3/2 Omega_m / N^3
 void require_particles(const Sim& s);
 int enqueue_steps(Sim& s, int k);  // k steps on s.stream, no wait, flags unchecked; CUBE_DONE at a_final
 int64_t footprint_bytes(const cube_params& p);
+// The moved-particle records of the steps about to be enqueued (before a capture, since it may
+// allocate), and giving them back.
+void ensure_records(Sim& s);
+void release_records(Sim& s);
 
 // ---- launchers (implemented in the .hip files) ---------------------------------------------
 bool fft_size_supported(int n);

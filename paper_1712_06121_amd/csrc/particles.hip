@@ -425,6 +425,10 @@ struct MoveArgs {
   // adaptive time steps: when set, the count pass raises amax[0] to the largest |v|^2 after the
   // kick and amax[1] to the largest |t|^2 of the interpolated gradient (FP32 bit patterns)
   uint32_t* amax;
+  // moved particles (step and drift passes): when set, the count pass writes every particle's new
+  // velocity, codes and displacement at its storage index, and k_place puts them in their new cells
+  float4* rec;
+  uint32_t* rec2;
   // gradient-tile scatter: polls of the LDS turn word after which a chunk stops waiting for its
   // turn and raises the count error (the wait then ends whatever the other wavefronts do)
   uint32_t turn_limit;
@@ -508,6 +512,18 @@ __device__ __forceinline__ void velocity_moments(const float* v, long long* q) {
       q[3] += __double2ll_rn(vd * vd * 16777216.0);
     }
   }
+}
+
+// Record of a moved particle, written by the count pass and read by k_place: the velocity after
+// the kick (FP32, as the encoding takes it), the new position codes and the displacement code
+// (z y x digits of k + 1 in base 3). 16 bytes with 1-byte positions; 2-byte ones put the x and y codes
+// into a second plane of 4 bytes.
+template <int NCHI>
+__device__ __forceinline__ void store_record(const MoveArgs& a, int64_t p, const float* v, const int* chi, int dcode) {
+  const uint32_t w = NCHI == 1 ? (uint32_t)(chi[0] | (chi[1] << 8) | (chi[2] << 16) | (dcode << 24))
+                               : (uint32_t)(chi[2] | (dcode << 16));
+  a.rec[p] = make_float4(v[0], v[1], v[2], __uint_as_float(w));
+  if constexpr (NCHI == 2) a.rec2[p] = (uint32_t)(chi[0] | (chi[1] << 16));
 }
 
 struct Moved {
@@ -830,6 +846,8 @@ __device__ __forceinline__ void move_count_tile(MoveArgs a, const unsigned lb) {
       const Moved m = move_particle<NCHI, NNU, MODE, PRE, MEAS>(a, ph, gd, s, p, li, g);
       const int dcode = (m.k[2] + 1) * 9 + (m.k[1] + 1) * 3 + (m.k[0] + 1);
       key = s * 27 + dcode;
+      if constexpr (MODE != 2)
+        if (a.rec) store_record<NCHI>(a, p, m.v, m.chi, dcode);
       r = (s % T + 1 + m.k[0]) + RG * ((s / T) % T + 1 + m.k[1]) + RG * RG * (s / (T * T) + 1 + m.k[2]);
       vm[0] = m.v[0];
       vm[1] = m.v[1];
@@ -1285,6 +1303,7 @@ __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
       physics(active, s, ci, o1, o2, chc, nuc, v, k, cq);
       const int dcode = (k[2] + 1) * 9 + (k[1] + 1) * 3 + (k[0] + 1);
       if constexpr (!SCATTER) {
+        if (a.rec && active) store_record<NCHI>(a, pc, v, cq, dcode);
         const uint32_t cbeg = pre[s], cend = pre[s + 1];
         long long q[4];
         velocity_moments(v, q);  // inactive lanes hold v = 0
@@ -1435,6 +1454,202 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
   const unsigned l = xcd_block(blockIdx.x, gridDim.x);
   const int b = box_of(t.first, t.nbox, l);
   move_dense_tile<NCHI, NNU, SCATTER, false>(t.args[b], l - t.first[b]);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Place: the scatter pass from the count pass's records. A workgroup of four wavefronts takes a tile
+// of 4^3 coarse cells, each wavefront one z layer of 16 cells in storage order, 64 particles at a
+// time, so the running destination per (source cell, displacement) in LDS is advanced by one
+// wavefront only and needs no ordering between wavefronts: the order is that of the recomputing
+// passes. Against recomputing the move, the potential tile (42 to 83 bytes per particle where cells
+// hold few), the interpolation and the kick are gone for 16 bytes per particle written and read:
+// 256^3 particles on 512^3 cells 850 -> 338 us, 512^3 on 512^3 2253 -> 1340 us, for 60 and 110 us
+// more in the count pass. Workgroups of 512 and 1024 threads, and half as many of them on a CU, take
+// the same time: it is bound by the rate of its byte stores, each of which splits into one
+// request per destination line.
+// ---------------------------------------------------------------------------------------------
+constexpr int PLACE_BLK = 256;
+
+template <int NCHI, int NNU, bool PID>
+__device__ __forceinline__ void place_tile(const MoveArgs& a, const unsigned lb) {
+  using CT = chi_t<NCHI>;
+  using NT = nu_t<NNU>;
+  constexpr int WC = TC / (PLACE_BLK / 64);  // cells per wavefront
+  __shared__ uint32_t next[TC * 27];  // next destination per (own cell, displacement)
+  __shared__ uint32_t offr[RC];       // of the tile's and ring's new cells: offset,
+  __shared__ float4 stat[RC];         // mean velocity and encode scale
+  __shared__ float edges_lds[NNU == 1 ? 256 : 1];
+  __shared__ int8_t bucket_lds[NNU == 1 ? 1024 : 1];
+  const uint32_t failed = __atomic_load_n(a.flags, __ATOMIC_RELAXED);
+  const TileGeom g = tile_of(lb, a.nt);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t nc = (uint32_t)a.nc;
+  if (threadIdx.x < RC) {
+    const int r = threadIdx.x;
+    const uint32_t nx = (uint32_t)wrapi(g.cx0 + r % RG - 1, a.nc), ny = (uint32_t)wrapi(g.cy0 + (r / RG) % RG - 1, a.nc);
+    const uint32_t nz = (uint32_t)wrapi(g.cz0 + r / (RG * RG) - 1, a.nc);
+    const uint32_t c = nx + nc * (ny + nc * nz);
+    offr[r] = (uint32_t)a.off_n[c];  // below 2^31 (the records' limit on the capacity)
+    stat[r] = make_float4(a.vc_n[c], (a.vc_n + a.nc3)[c], (a.vc_n + 2 * a.nc3)[c], a.vinv[c]);
+  }
+  // every slot of the tile requested at once: wavefront w takes the displacements w, w + 4, ...
+  constexpr int NS = (27 + PLACE_BLK / 64 - 1) / (PLACE_BLK / 64);
+  uint32_t sl[NS];
+  int ox, oy, oz;
+  tile_xyz(lane, ox, oy, oz);
+  {
+    const uint32_t c = (uint32_t)(g.cx0 + ox) + nc * ((uint32_t)(g.cy0 + oy) + nc * (uint32_t)(g.cz0 + oz));
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+      const int d = wave + k * (PLACE_BLK / 64);
+      if (d < 27) sl[k] = (a.mig + (int64_t)d * a.nc3)[c];
+    }
+  }
+  // lane q < WC: the wavefront's q-th cell (count, storage start)
+  uint32_t cnt = 0, beg = 0;
+  if (lane < WC) {
+    int qx, qy, qz;
+    tile_xyz(WC * wave + lane, qx, qy, qz);
+    const uint32_t c = (uint32_t)(g.cx0 + qx) + nc * ((uint32_t)(g.cy0 + qy) + nc * (uint32_t)(g.cz0 + qz));
+    cnt = a.cnt[c];
+    beg = (uint32_t)a.off[c];
+  }
+  if constexpr (NNU == 1) {
+    static_assert(PLACE_BLK == 256, "one edge per thread");
+    edges_lds[threadIdx.x] = a.tedge[threadIdx.x];
+    for (int i = threadIdx.x; i < a.nbucket; i += PLACE_BLK) bucket_lds[i] = (int8_t)a.tbucket[i];
+  }
+  const float* const edges = NNU == 1 ? edges_lds : a.tedge;
+  using BT = std::conditional_t<NNU == 1, int8_t, int16_t>;
+  const BT* bucket;
+  if constexpr (NNU == 1) bucket = bucket_lds;
+  else bucket = a.tbucket;
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(failed)) return;  // a failed step is not applied
+  const int rbase = (ox + 1) + RG * (oy + 1) + RG * RG * (oz + 1);  // ring index of own cell `lane`
+#pragma unroll
+  for (int k = 0; k < NS; ++k) {
+    const int d = wave + k * (PLACE_BLK / 64);
+    if (d < 27) next[lane * 27 + d] = offr[rbase + (d % 3 - 1) + RG * ((d / 3) % 3 - 1) + RG * RG * (d / 9 - 1)] + sl[k];
+  }
+  // the wavefront's cells: exclusive prefix of the counts in the lanes
+  uint32_t inc = cnt;
+#pragma unroll
+  for (int o = 1; o < WC; o <<= 1) {
+    const uint32_t y = (uint32_t)__shfl_up((int)inc, o, 64);
+    if (lane >= o) inc += y;
+  }
+  const uint32_t pre = inc - cnt;   // lanes from WC on hold the total
+  const uint32_t rel = beg - pre;   // storage index of a cell's particle i: rel + i
+  const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, WC - 1);
+  __syncthreads();
+  CT* const chi_n = static_cast<CT*>(a.chi_n);
+  NT* const nu_n = static_cast<NT*>(a.nu_n);
+  int ec = 0;  // the cell of the chunk's first particle
+  // cell of each lane's particle of the chunk at c0, its storage index, and the lanes of its cell
+  auto locate = [&](uint32_t c0, int& sc, uint32_t& p, unsigned long long& own) {
+    uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)inc, ec);
+    while (end <= c0) end = (uint32_t)__builtin_amdgcn_readlane((int)inc, ++ec);
+    const uint32_t i = c0 + (uint32_t)lane, left = tot - c0;
+    sc = ec;
+    uint32_t rl = (uint32_t)__builtin_amdgcn_readlane((int)rel, ec);
+    own = end - c0 >= 64u ? ~0ull : (1ull << (end - c0)) - 1ull;
+    for (int q = ec + 1; q < WC && end < c0 + 64u; ++q) {
+      const uint32_t b = end;  // first particle of cell q
+      end = (uint32_t)__builtin_amdgcn_readlane((int)inc, q);
+      const unsigned long long m = (end - c0 >= 64u ? ~0ull : (1ull << (end - c0)) - 1ull) & ~((1ull << (b - c0)) - 1ull);
+      const uint32_t rq = (uint32_t)__builtin_amdgcn_readlane((int)rel, q);
+      if (i >= b) {
+        sc = q;
+        rl = rq;
+        own = m;
+      }
+    }
+    // lanes past the end read the last particle
+    p = rl + ((uint32_t)lane < left ? i : tot - 1u);
+  };
+  float4 rn = make_float4(0.f, 0.f, 0.f, 0.f);
+  uint32_t r2n = 0u, pn = 0u;
+  uint64_t idn = 0u;
+  int sn = 0;
+  unsigned long long on = 0ull;
+  auto request = [&]() {
+    rn = a.rec[pn];
+    if constexpr (NCHI == 2) r2n = a.rec2[pn];
+    if constexpr (PID) idn = particle_id<0>(a, g, 0, (int64_t)pn, 0u);
+  };
+  // one chunk; FULL: every lane holds a particle
+  auto chunk = [&](auto full, uint32_t c0) {
+    constexpr bool FULL = decltype(full)::value;
+    const float4 rc = rn;
+    const uint32_t r2 = r2n;
+    const uint64_t id = idn;
+    const int s = sn + WC * wave;
+    unsigned long long peers = on;
+    // the next chunk's records are requested before this chunk's stores are issued (past the end
+    // the request repeats a particle of this chunk)
+    if (c0 + 64u < tot) locate(c0 + 64u, sn, pn, on);
+    request();
+    const bool active = FULL || c0 + (uint32_t)lane < tot;
+    const uint32_t w = __float_as_uint(rc.w);
+    const uint32_t dc = NCHI == 1 ? w >> 24 : w >> 16;
+    if constexpr (!FULL) peers &= __ballot(active);
+#pragma unroll
+    for (int b = 0; b < 5; ++b) {
+      const bool bit = (dc >> b) & 1u;
+      const unsigned long long bb = __ballot(active && bit);
+      peers &= bit ? bb : ~bb;
+    }
+    const uint32_t rin = lanes_below(peers);
+    const uint32_t key = (uint32_t)s * 27u + dc;
+    // ring index of the new cell: dc = (kx + 1) + 3 (ky + 1) + 9 (kz + 1) gives
+    // (kx + 1) + 6 (ky + 1) + 36 (kz + 1) = dc + 3 [dc / 3] + 18 [dc / 9]
+    const uint32_t t3 = (dc * 11u) >> 5, t9 = (dc * 57u) >> 9;
+    const uint32_t cell = (uint32_t)((s & 3) + RG * ((s >> 2) & 3) + RG * RG * (s >> 4)) + dc + 3u * t3 + 18u * t9;
+    const uint32_t b0 = next[key];
+    const float4 st = stat[cell];
+    if (active && rin == 0u) next[key] = b0 + (uint32_t)__popcll(peers);
+    uint32_t dst = b0 + rin;
+    if (active && dst >= (uint32_t)a.cap) set_flag(a.flags, FLAG_COUNT);
+    dst = min(dst, (uint32_t)a.cap - 1u);
+    const float u[3] = {(rc.x - st.x) * st.w, (rc.y - st.y) * st.w, (rc.z - st.z) * st.w};
+    const uint32_t ch[3] = {NCHI == 1 ? w & 255u : r2 & 65535u, NCHI == 1 ? (w >> 8) & 255u : r2 >> 16,
+                            NCHI == 1 ? (w >> 16) & 255u : w & 65535u};
+    int nu[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) nu[d] = encode_nu<false>(u[d], edges, bucket, a.nbucket, a.vhalf);
+    if (active) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        (nu_n + d * a.cap)[dst] = (NT)nu[d];
+        (chi_n + d * a.cap)[dst] = (CT)ch[d];
+      }
+      if constexpr (PID) store_id(a, dst, id);
+    }
+  };
+  if (tot > 0u) {
+    locate(0u, sn, pn, on);
+    request();
+  }
+  // whole chunks first: their stores are unconditional, so the wait for the next chunk's records
+  // is for a known number of later stores and does not wait for these (with a branch around the
+  // stores the compiler drains them every chunk: 1345 us for 512^3 particles)
+  uint32_t c0 = 0;
+  for (; c0 + 64u <= tot; c0 += 64u) chunk(std::true_type{}, c0);
+  if (c0 < tot) chunk(std::false_type{}, c0);
+}
+
+template <int NCHI, int NNU, bool PID>
+__global__ __launch_bounds__(PLACE_BLK) void k_place(MoveArgs a) {
+  place_tile<NCHI, NNU, PID>(a, xcd_block(blockIdx.x, gridDim.x));
+}
+
+template <int NCHI, int NNU, bool PID>
+__global__ __launch_bounds__(PLACE_BLK) void k_place_boxes(BoxTable<MoveArgs> t) {
+  const unsigned l = xcd_block(blockIdx.x, gridDim.x);
+  const int b = box_of(t.first, t.nbox, l);
+  place_tile<NCHI, NNU, PID>(t.args[b], l - t.first[b]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1916,6 +2131,11 @@ void launch_raise_flag(Sim& s, hipStream_t st, uint32_t f, bool dev_sched, int a
   CUBE_HIP(hipGetLastError());
 }
 
+// whether a step's scatter places the count pass's records (k_place) instead of recomputing the
+// move: when the record buffer is there; a poll limit other than the default asks for the ordered
+// scatter it belongs to
+static bool use_records(const Sim& s) { return s.rec && s.turn_limit == kTurnLimit; }
+
 // the move passes' arguments from the state of parity cur to the other (no step maxima, no
 // initial-condition fields)
 static MoveArgs move_args(const Sim& s, int cur, float kfac, float dfac, bool dev_sched) {
@@ -1955,6 +2175,10 @@ static MoveArgs move_args(const Sim& s, int cur, float kfac, float dfac, bool de
   a.pid_n = s.pid[nxt];
   a.pid_bytes = s.pid_bytes;
   a.amax = nullptr;
+  if (use_records(s)) {
+    a.rec = reinterpret_cast<float4*>(s.rec);
+    a.rec2 = reinterpret_cast<uint32_t*>(s.rec + sizeof(float4) * (size_t)s.capacity);
+  }
   a.turn_limit = s.turn_limit;
   return a;
 }
@@ -2004,7 +2228,9 @@ void launch_move(Sim& s, int mode, float kfac, float dfac, float* const* psi, fl
   } while (0)
 #define CUBE_SCATTER(X, V)                                                                      \
   do {                                                                                          \
-    if (tile_scatter) k_move_dense<X, V, true><<<grid, 1024, 0, st>>>(a);                        \
+    if (mode != 2 && a.rec && a.pid_bytes) k_place<X, V, true><<<grid, PLACE_BLK, 0, st>>>(a);   \
+    else if (mode != 2 && a.rec) k_place<X, V, false><<<grid, PLACE_BLK, 0, st>>>(a);            \
+    else if (tile_scatter) k_move_dense<X, V, true><<<grid, 1024, 0, st>>>(a);                   \
     else if (mode == 0) k_move_scatter<X, V, 0, false, 512><<<grid, 512, 0, st>>>(a);            \
     else if (mode == 1) k_move_scatter<X, V, 1, false, 256><<<grid, 256, 0, st>>>(a);            \
     else k_move_scatter<X, V, 2, false, 256><<<grid, 256, 0, st>>>(a);                           \
@@ -2114,28 +2340,32 @@ void ensemble_deposit(EnsembleStep& es, const std::vector<Sim*>& boxes) {
 
 void ensemble_move(EnsembleStep& es, const std::vector<Sim*>& boxes) {
   const EnsembleStep* e = &es;
-  // one pass over the boxes grouped by codec and kernel (gradient tile or per-corner gradient)
+  // one pass over the boxes grouped by codec and kernel (0 per-corner gradient, 1 gradient tile, 2 the
+  // scatter from records, 3 that with particle IDs)
   auto pass = [&](bool scatter) {
     for (int xv = 0; xv < 4; ++xv)
-      for (int tile = 0; tile <= 1; ++tile) {
+      for (int tile = 0; tile <= 3; ++tile) {
         const int nchi = 1 + (xv >> 1), nnu = 1 + (xv & 1);
         std::vector<MoveArgs> args;
         std::vector<uint32_t> per;
         for (Sim* s : boxes) {
           bool tc, ts;
           move_kernels(*s, 0, &tc, &ts);
-          if (s->nchi != nchi || s->nnu != nnu || (scatter ? ts : tc) != (tile != 0)) continue;
+          const int kern = scatter ? (use_records(*s) ? (s->pid_bytes ? 3 : 2) : (ts ? 1 : 0)) : (tc ? 1 : 0);
+          if (s->nchi != nchi || s->nnu != nnu || kern != tile) continue;
           args.push_back(move_args(*s, s->cur, 0.0f, 0.0f, true));
           const int64_t nt = s->nc / T;
           per.push_back((uint32_t)(nt * nt * nt));
         }
         if (args.empty()) continue;
-        const StagedBoxes g = stage_boxes(es, args, per, tile ? 1024 : 512);
+        const StagedBoxes g = stage_boxes(es, args, per, tile >= 2 ? PLACE_BLK : (tile ? 1024 : 512));
         es.launches.push_back([e, g, nchi, nnu, tile, scatter](hipStream_t st) {
           const BoxTable<MoveArgs> t = table_of<MoveArgs>(e, g);
 #define CUBE_PASS(X, V)                                                                                 \
   do {                                                                                                  \
-    if (tile && scatter) k_move_dense_boxes<X, V, true><<<g.blocks, 1024, 0, st>>>(t);                   \
+    if (tile == 3) k_place_boxes<X, V, true><<<g.blocks, PLACE_BLK, 0, st>>>(t);                         \
+    else if (tile == 2) k_place_boxes<X, V, false><<<g.blocks, PLACE_BLK, 0, st>>>(t);                   \
+    else if (tile && scatter) k_move_dense_boxes<X, V, true><<<g.blocks, 1024, 0, st>>>(t);                   \
     else if (tile) k_move_dense_boxes<X, V, false><<<g.blocks, 1024, 0, st>>>(t);                        \
     else if (scatter) k_move_scatter_boxes<X, V, 0, false, 512><<<g.blocks, 512, 0, st>>>(t);            \
     else k_move_count_boxes<X, V, 0, false, 512><<<g.blocks, 512, 0, st>>>(t);                           \

@@ -86,7 +86,10 @@ void admit(cube_server& srv, Job& j) {
   srv.in_use += j.footprint;
   j.state = ACTIVE;
   int rc = cube_create(&j.p, j.stream, srv.has_alloc ? &srv.alloc : nullptr, &j.sim);
-  if (rc == CUBE_OK) rc = cube_init_ic(j.sim);
+  if (rc == CUBE_OK) {
+    j.sim->s.rec_in_footprint = true;  // admission counts footprints
+    rc = cube_init_ic(j.sim);
+  }
   if (rc != CUBE_OK) {
     j.rc = rc;
     j.error = j.sim ? cube_last_error(j.sim) : cube_last_error(nullptr);
