@@ -323,7 +323,7 @@ void ic_fields(Sim& s, float** psi, float** wk_out, std::vector<void*>& temps, b
   }
   for (int d = 0; d < 3; ++d) {
     if (d == 0 && use_state_buffer && s.pbytes >= fbytes) {
-      psi[d] = static_cast<float*>(s.chi[s.cur]);  // the lattice pre-state reads no stored codes
+      psi[d] = static_cast<float*>(s.codes[s.cur]);  // the lattice pre-state reads no stored codes
       continue;
     }
     psi[d] = static_cast<float*>(s.dmalloc(fbytes));
@@ -513,9 +513,7 @@ int cube_create(const cube_params* params, void* stream, const cube_allocator* a
     // particle state, double buffered
     for (int b = 0; b < 2; ++b) {
       const size_t pb = (size_t)3 * s.capacity * (s.nchi + s.nnu);
-      char* buf = static_cast<char*>(s.dmalloc(pb));
-      s.chi[b] = buf;
-      s.nu[b] = buf + (size_t)3 * s.capacity * s.nchi;
+      s.codes[b] = s.dmalloc(pb);
       s.pbytes = pb;
       s.cnt[b] = static_cast<uint32_t*>(s.dmalloc(sizeof(uint32_t) * s.nc3));
       s.off[b] = static_cast<uint64_t*>(s.dmalloc(sizeof(uint64_t) * (s.nc3 + 1)));
@@ -1009,14 +1007,11 @@ int cube_get_state(cube_sim* sim, cube_state_view* out) {
     const int c = s.cur;
     const hipStream_t st = s.stream;
     CUBE_HIP(hipMemcpyAsync(out->cnt, s.cnt[c], sizeof(uint32_t) * s.nc3, hipMemcpyDefault, st));
-    for (int d = 0; d < 3; ++d) {
-      CUBE_HIP(hipMemcpyAsync(static_cast<char*>(out->chi) + (size_t)d * s.n * s.nchi,
-                              static_cast<char*>(s.chi[c]) + (size_t)d * s.capacity * s.nchi, (size_t)s.n * s.nchi,
-                              hipMemcpyDefault, st));
-      CUBE_HIP(hipMemcpyAsync(static_cast<char*>(out->nu) + (size_t)d * s.n * s.nnu,
-                              static_cast<char*>(s.nu[c]) + (size_t)d * s.capacity * s.nnu, (size_t)s.n * s.nnu,
-                              hipMemcpyDefault, st));
-    }
+    void *chi, *nu;
+    cube::staged_planes(s, &chi, &nu);
+    cube::launch_unpack_codes(s, st);
+    CUBE_HIP(hipMemcpyAsync(out->chi, chi, (size_t)3 * s.n * s.nchi, hipMemcpyDefault, st));
+    CUBE_HIP(hipMemcpyAsync(out->nu, nu, (size_t)3 * s.n * s.nnu, hipMemcpyDefault, st));
     CUBE_HIP(hipMemcpyAsync(out->vc, s.vc[c], sizeof(float) * 3 * s.nc3, hipMemcpyDefault, st));
     CUBE_HIP(hipMemcpyAsync(out->vs, s.vs[c], sizeof(float) * s.nc3, hipMemcpyDefault, st));
     CUBE_HIP(hipStreamSynchronize(st));
@@ -1047,14 +1042,11 @@ int cube_set_state(cube_sim* sim, const cube_state_view* in) {
     s.n = in->n;
     CUBE_HIP(hipMemcpyAsync(s.cnt[c], in->cnt, sizeof(uint32_t) * s.nc3, hipMemcpyHostToDevice, st));
     CUBE_HIP(hipMemcpyAsync(s.off[c], off.data(), sizeof(uint64_t) * (s.nc3 + 1), hipMemcpyHostToDevice, st));
-    for (int d = 0; d < 3; ++d) {
-      CUBE_HIP(hipMemcpyAsync(static_cast<char*>(s.chi[c]) + (size_t)d * s.capacity * s.nchi,
-                              static_cast<const char*>(in->chi) + (size_t)d * s.n * s.nchi, (size_t)s.n * s.nchi,
-                              hipMemcpyHostToDevice, st));
-      CUBE_HIP(hipMemcpyAsync(static_cast<char*>(s.nu[c]) + (size_t)d * s.capacity * s.nnu,
-                              static_cast<const char*>(in->nu) + (size_t)d * s.n * s.nnu, (size_t)s.n * s.nnu,
-                              hipMemcpyHostToDevice, st));
-    }
+    void *chi, *nu;
+    cube::staged_planes(s, &chi, &nu);
+    CUBE_HIP(hipMemcpyAsync(chi, in->chi, (size_t)3 * s.n * s.nchi, hipMemcpyHostToDevice, st));
+    CUBE_HIP(hipMemcpyAsync(nu, in->nu, (size_t)3 * s.n * s.nnu, hipMemcpyHostToDevice, st));
+    cube::launch_pack_codes(s, st);
     CUBE_HIP(hipMemcpyAsync(s.vc[c], in->vc, sizeof(float) * 3 * s.nc3, hipMemcpyHostToDevice, st));
     CUBE_HIP(hipMemcpyAsync(s.vs[c], in->vs, sizeof(float) * s.nc3, hipMemcpyHostToDevice, st));
     CUBE_HIP(hipStreamSynchronize(st));

@@ -111,8 +111,7 @@ struct Sim {
   int64_t dev_bytes = 0;
 
   // particle state, double buffered: [cur] is current
-  void* chi[2] = {nullptr, nullptr};   // 3 planes x capacity x nchi bytes
-  void* nu[2] = {nullptr, nullptr};    // 3 planes x capacity x nnu bytes
+  void* codes[2] = {nullptr, nullptr};  // position and velocity codes, 3 (nchi + nnu) bytes x capacity (particles.hip)
   uint32_t* cnt[2] = {nullptr, nullptr};
   uint64_t* off[2] = {nullptr, nullptr};  // nc3 + 1 (exclusive prefix, last = N)
   float* vc[2] = {nullptr, nullptr};      // 3 x nc3
@@ -209,7 +208,7 @@ struct Sim {
   double timings[16] = {};
   int timing_calls = 0;
 
-  size_t pbytes = 0;  // bytes of one particle-state buffer (chi and nu planes)
+  size_t pbytes = 0;  // bytes of one particle-state buffer (its codes)
 
   void* dmalloc(size_t bytes);
   void dfree(void* p);
@@ -278,6 +277,11 @@ void sort_pairs_by_key(Sim& s, uint32_t* key, uint32_t* val, uint32_t* key_alt, 
 int64_t select_at_least_255(Sim& s, const uint32_t* cnt, int64_t n, uint32_t* out, hipStream_t st);
 // largest |v|^2 of the current state (uses amax as scratch; synchronises)
 float launch_state_speed2(Sim& s, hipStream_t st);
+// the current codes as the checkpoint's planes (chi: 3 planes of n codes, nu: 3 planes of n) into the
+// other state buffer, and back: staged_planes says where in it
+void staged_planes(const Sim& s, void** chi, void** nu);
+void launch_unpack_codes(Sim& s, hipStream_t st);
+void launch_pack_codes(Sim& s, hipStream_t st);
 // particle IDs 0 .. n-1 in storage order (when IDs are enabled)
 void launch_pid_iota(Sim& s, hipStream_t st);
 void launch_power_finish(Sim& s, int nbins, double* k, double* pk, double* nmodes);

@@ -3,8 +3,8 @@
 // lattice move and the load path.
 //
 // Storage (Sec. 2.1-2.2): particles are cell ordered; position codes chi (Eq. (chi)) and velocity
-// codes nu (Eq. (nu)) are structure-of-arrays byte planes; per coarse cell the count, the storage
-// offset, the mean velocity v_c and the decode scale sigma sqrt(2/pi) of Eq. (v).
+// codes nu (Eq. (nu)) are packed into words of two or three planes (Codes below); per coarse cell the
+// count, the storage offset, the mean velocity v_c and the decode scale sigma sqrt(2/pi) of Eq. (v).
 //
 // All kernels work on tiles of T^3 coarse cells (one workgroup per tile). Deposit gathers: the
 // workgroup that owns a tile of fine cells reads the particles of its tile and of the ring of
@@ -48,6 +48,99 @@ template <int NCHI>
 using chi_t = std::conditional_t<NCHI == 1, uint8_t, uint16_t>;
 template <int NNU>
 using nu_t = std::conditional_t<NNU == 1, int8_t, int16_t>;
+
+// The codes of one particle as they lie in memory. The first plane's word (4 bytes with 1-byte
+// positions, 8 with 2-byte ones) holds the three position codes and fills up with velocity codes;
+// the rest of these follow in planes of 4, 2 or 1 bytes:
+//   x1v1  [chi0 chi1 chi2 nu0] [nu1 nu2]            x1v2  [chi0 chi1 chi2 nu0lo] [nu1 nu2] [nu0hi]
+//   x2v1  [chi0 chi1 chi2 nu0 nu1] [nu2]            x2v2  [chi0 chi1 chi2 nu0] [nu1 nu2]
+// that is 3 (n_chi + n_nu) bytes a particle in all, each plane `cap` words long and aligned to its
+// word. A plane per code cost six byte loads and six byte stores a particle, and each store
+// instruction of a scatter makes one request per destination line (about a dozen), which bounded it.
+// With 512^3 x1v1 particles: scatter 1340 -> 990 us, deposit, which reads the first plane only, 1436 ->
+// 1075 us early and 1793 -> 1369 us clustered.
+template <int NCHI, int NNU>
+struct Codes {
+  uint32_t a0, a1, b, c;  // first plane (a1: 2-byte positions), second, third
+
+  __device__ __forceinline__ void load_chi(const void* base, int64_t p) {
+    if constexpr (NCHI == 1) {
+      a0 = static_cast<const uint32_t*>(base)[p];
+    } else {
+      const uint2 w = static_cast<const uint2*>(base)[p];
+      a0 = w.x;
+      a1 = w.y;
+    }
+  }
+  __device__ __forceinline__ void load(const void* base, int64_t cap, int64_t p) {
+    load_chi(base, p);
+    const char* const rest = static_cast<const char*>(base) + cap * (NCHI == 1 ? 4 : 8);
+    if constexpr (NCHI == 1 && NNU == 1) b = reinterpret_cast<const uint16_t*>(rest)[p];
+    if constexpr (NNU == 2) b = reinterpret_cast<const uint32_t*>(rest)[p];
+    if constexpr (NCHI == 1 && NNU == 2) c = reinterpret_cast<const uint8_t*>(rest + cap * 4)[p];
+    if constexpr (NCHI == 2 && NNU == 1) c = reinterpret_cast<const uint8_t*>(rest)[p];
+  }
+  __device__ __forceinline__ void store(void* base, int64_t cap, int64_t p) const {
+    if constexpr (NCHI == 1) static_cast<uint32_t*>(base)[p] = a0;
+    else static_cast<uint2*>(base)[p] = make_uint2(a0, a1);
+    char* const rest = static_cast<char*>(base) + cap * (NCHI == 1 ? 4 : 8);
+    if constexpr (NCHI == 1 && NNU == 1) reinterpret_cast<uint16_t*>(rest)[p] = (uint16_t)b;
+    if constexpr (NNU == 2) reinterpret_cast<uint32_t*>(rest)[p] = b;
+    if constexpr (NCHI == 1 && NNU == 2) reinterpret_cast<uint8_t*>(rest + cap * 4)[p] = (uint8_t)c;
+    if constexpr (NCHI == 2 && NNU == 1) reinterpret_cast<uint8_t*>(rest)[p] = (uint8_t)c;
+  }
+  __device__ __forceinline__ void chi(int* ch) const {
+    if constexpr (NCHI == 1) {
+      ch[0] = (int)(a0 & 255u);
+      ch[1] = (int)((a0 >> 8) & 255u);
+      ch[2] = (int)((a0 >> 16) & 255u);
+    } else {
+      ch[0] = (int)(a0 & 65535u);
+      ch[1] = (int)(a0 >> 16);
+      ch[2] = (int)(a1 & 65535u);
+    }
+  }
+  __device__ __forceinline__ void nu(int* n) const {
+    const uint32_t t = (NCHI == 1 ? a0 >> 24 : a1 >> 16);  // what follows the positions in the first plane
+    if constexpr (NNU == 1) {
+      n[0] = (int)(int8_t)t;
+      n[1] = (int)(int8_t)(NCHI == 1 ? b : t >> 8);
+      n[2] = (int)(int8_t)(NCHI == 1 ? b >> 8 : c);
+    } else {
+      n[0] = (int)(int16_t)(NCHI == 1 ? t | (c << 8) : t);
+      n[1] = (int)(int16_t)b;
+      n[2] = (int)(int16_t)(b >> 16);
+    }
+  }
+  // position codes already packed: chi0 | chi1 << 8 | chi2 << 16 in w, or chi0 | chi1 << 16 in w, chi2 in w2
+  __device__ __forceinline__ void pack(uint32_t w, uint32_t w2, const int* n) {
+    a0 = w;
+    a1 = w2;
+    if constexpr (NNU == 1) {
+      const uint32_t n0 = (uint32_t)n[0] & 255u, n1 = (uint32_t)n[1] & 255u, n2 = (uint32_t)n[2] & 255u;
+      if constexpr (NCHI == 1) {
+        a0 |= n0 << 24;
+        b = n1 | (n2 << 8);
+      } else {
+        a1 |= (n0 << 16) | (n1 << 24);
+        c = n2;
+      }
+    } else {
+      const uint32_t n0 = (uint32_t)n[0] & 65535u;
+      b = ((uint32_t)n[1] & 65535u) | ((uint32_t)n[2] << 16);
+      if constexpr (NCHI == 1) {
+        a0 |= n0 << 24;
+        c = n0 >> 8;
+      } else {
+        a1 |= n0 << 16;
+      }
+    }
+  }
+  __device__ __forceinline__ void set(const int* ch, const int* n) {
+    if constexpr (NCHI == 1) pack((uint32_t)(ch[0] | (ch[1] << 8) | (ch[2] << 16)), 0u, n);
+    else pack((uint32_t)ch[0] | ((uint32_t)ch[1] << 16), (uint32_t)ch[2], n);
+  }
+};
 
 __device__ __forceinline__ int wrapi(int x, int n) { return x < 0 ? x + n : (x >= n ? x - n : x); }
 
@@ -186,7 +279,7 @@ __device__ __forceinline__ TileGeom tile_of(int b, int nt) {
 // CIC deposit (Sec. 3 "CIC"; cell centres at i + 1/2), exact integer weights, gather by tile.
 // ---------------------------------------------------------------------------------------------
 struct DepArgs {
-  const void* chi;
+  const void* codes;
   const uint32_t* cnt;
   const uint64_t* off;
   int64_t cap;
@@ -213,7 +306,6 @@ __device__ __forceinline__ int slot_of(int p) { return ((p % NSLOT) + NSLOT) % N
 // more mass: they are converted once to FP32 delta, written, and their slots reused.
 template <int NCHI, int BLK>
 __device__ __forceinline__ void deposit_column(const DepArgs& a, const unsigned lb) {
-  using CT = chi_t<NCHI>;
   constexpr int SH = 8 * NCHI - 1;
   __shared__ unsigned long long rho[NSLOT * DF * DF];
   __shared__ uint32_t pre[DRC + 1];
@@ -251,9 +343,6 @@ __device__ __forceinline__ void deposit_column(const DepArgs& a, const unsigned 
   __syncthreads();
   const bool narrow = NCHI == 1 && smax <= 255u;
   uint32_t* rho32 = reinterpret_cast<uint32_t*>(rho);
-  const CT* cx = static_cast<const CT*>(a.chi);
-  const CT* cy = cx + a.cap;
-  const CT* cz = cy + a.cap;
   for (int sz = cz0 - 1; sz <= cz1; ++sz) {
     uint32_t cntv = 0;
     if (threadIdx.x < DRC) {
@@ -274,19 +363,19 @@ __device__ __forceinline__ void deposit_column(const DepArgs& a, const unsigned 
     auto deposit_layer = [&](auto* acc) {
     using A = typename std::remove_pointer<decltype(acc)>::type;
     // source cell and codes of the layer's it-th particle
-    auto fetch = [&](uint32_t it, int& s, int* ch) {
+    using Word = Codes<NCHI, 1>;  // its first plane is the same for every velocity code
+    auto fetch = [&](uint32_t it, int& s, Word& w) {
       // interleaved: lane l of the w-th group of 64 takes particle l * (total / 64) + w, so the lanes
       // of one wavefront hold particles of different cells (a bijection on [0, 64 * (total / 64)))
       const uint32_t i = (a.interleave && it < 64 * q64) ? (it % 64) * q64 + it / 64 : it;
       s = owner[i >> osh];
       while (pre[s + 1] <= i) ++s;
-      const int64_t p = (int64_t)start[s] + (i - pre[s]);
-      ch[0] = (int)cx[p];
-      ch[1] = (int)cy[p];
-      ch[2] = (int)cz[p];
+      w.load_chi(a.codes, (int64_t)start[s] + (i - pre[s]));
     };
     // CIC of one particle with source cell s and codes ch
-    auto deposit_one = [&](const int s, const int* ch) {
+    auto deposit_one = [&](const int s, const Word& w) {
+      int ch[3];
+      w.chi(ch);
       // the three codes are needed here on every path: without this the compiler may move their
       // uses into the conditional corners and then wait conservatively for later loads as well
       asm volatile("" ::"v"(ch[0]), "v"(ch[1]), "v"(ch[2]));
@@ -316,8 +405,8 @@ __device__ __forceinline__ void deposit_column(const DepArgs& a, const unsigned 
           for (int dx = 0; dx < 2; ++dx) {
             const int x = i0[0] + dx;
             if (x < 0 || x >= DF) continue;
-            const A w = NCHI == 1 ? (A)(wzy * wx2[dx]) : (A)((unsigned long long)wzy * (unsigned long long)wx2[dx]);
-            atomicAdd(&acc[sb + y * DF + x], w);
+            const A m = NCHI == 1 ? (A)(wzy * wx2[dx]) : (A)((unsigned long long)wzy * (unsigned long long)wx2[dx]);
+            atomicAdd(&acc[sb + y * DF + x], m);
           }
         }
       }
@@ -329,7 +418,8 @@ __device__ __forceinline__ void deposit_column(const DepArgs& a, const unsigned 
     // that the wait for the current codes never waits for the next ones.
     if (total > 0) {
       const uint32_t last = total - 1;
-      int s0, s1, ch0[3], ch1[3];
+      int s0, s1;
+      Word ch0, ch1;
       fetch(min((uint32_t)threadIdx.x, last), s0, ch0);
       for (uint32_t it = threadIdx.x; it < total; it += 2 * BLK) {
         fetch(min(it + BLK, last), s1, ch1);
@@ -382,14 +472,12 @@ __global__ __launch_bounds__(BLK) void k_deposit_boxes(BoxTable<DepArgs> t) {
 // MODE 2: initial conditions (lattice + Zel'dovich displacement).
 // ---------------------------------------------------------------------------------------------
 struct MoveArgs {
-  const void* chi;
-  const void* nu;
+  const void* codes;
   const uint32_t* cnt;
   const uint64_t* off;
   const float* vc;
   const float* vs;
-  void* chi_n;
-  void* nu_n;
+  void* codes_n;
   const uint64_t* off_n;
   const float* vc_n;
   const float* vinv;
@@ -594,8 +682,6 @@ __device__ __forceinline__ bool new_cell(float ln, float vd, uint32_t* flags, in
 template <int NCHI, int NNU, int MODE, bool PRE, bool MEAS = false>
 __device__ __forceinline__ Moved move_particle(const MoveArgs& a, const float* ph, const float* gd, int s, int64_t p,
                                                uint32_t li, const TileGeom& g) {
-  using CT = chi_t<NCHI>;
-  using NT = nu_t<NNU>;
   constexpr int SH = 8 * NCHI - 1;
   const int o[3] = {s % T, (s / T) % T, s / (T * T)};
   const int64_t c = (g.cx0 + o[0]) + (int64_t)a.nc * ((g.cy0 + o[1]) + (int64_t)a.nc * (g.cz0 + o[2]));
@@ -617,15 +703,16 @@ __device__ __forceinline__ Moved move_particle(const MoveArgs& a, const float* p
       l[d] = l0 + ps;
     }
   } else {
-    const CT* chi = static_cast<const CT*>(a.chi);
-    const NT* nu = static_cast<const NT*>(a.nu);
     const float unit = (float)(1.0 / (double)(1 << SH));
-    int ch[3];
+    Codes<NCHI, NNU> w;
+    w.load(a.codes, a.cap, p);
+    int ch[3], nuc[3];
+    w.chi(ch);
+    w.nu(nuc);
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-      ch[d] = (int)chi[d * a.cap + p];
       l[d] = (float)(2 * ch[d] + 1) * unit;
-      int nuv = (int)nu[d * a.cap + p];
+      int nuv = nuc[d];
       nuv = nuv < -a.vhalf ? -a.vhalf : (nuv > a.vhalf ? a.vhalf : nuv);
       v[d] = __builtin_fmaf(a.vs[c], a.tdec[nuv + a.vhalf], a.vc[d * a.nc3 + c]);
     }
@@ -961,8 +1048,6 @@ __device__ __forceinline__ int encode_nu(float u, const float* ext, const BT* bu
 template <int NCHI, int NNU, int MODE, bool PRE, int NTH>
 __device__ __forceinline__ void move_scatter_tile(MoveArgs a, const unsigned lb) {
   resolve_factors(a);
-  using CT = chi_t<NCHI>;
-  using NT = nu_t<NNU>;
   __shared__ float ph[MoveLds<MODE, PRE>::kPh];
   __shared__ float gd[MoveLds<MODE, PRE>::kGd];
   __shared__ uint32_t grp[TC * 27];
@@ -986,8 +1071,6 @@ __device__ __forceinline__ void move_scatter_tile(MoveArgs a, const unsigned lb)
   const int16_t* bucket = (NNU == 1) ? bucket_lds : a.tbucket;
   const uint32_t total = own_cells<MODE>(a, g, pre, start, wsum);
   if (__builtin_amdgcn_readfirstlane(failed)) return;  // a failed step is not applied
-  CT* chi_n = static_cast<CT*>(a.chi_n);
-  NT* nu_n = static_cast<NT*>(a.nu_n);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const unsigned long long lt = (1ull << lane) - 1ull;
   int c0, c1;
@@ -1033,12 +1116,15 @@ __device__ __forceinline__ void move_scatter_tile(MoveArgs a, const unsigned lb)
       const uint64_t dst = a.off_n[cn] + a.mig[(int64_t)dcode * a.nc3 + co] + gbase + (uint32_t)rin;
       if (dst < (uint64_t)a.cap) {
         const float inv = a.vinv[cn];
+        int nu[3];
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
           const float u = (m.v[d] - a.vc_n[d * a.nc3 + cn]) * inv;
-          nu_n[d * a.cap + dst] = (NT)encode_nu<false>(u, edges, bucket, a.nbucket, a.vhalf);
-          chi_n[d * a.cap + dst] = (CT)m.chi[d];
+          nu[d] = encode_nu<false>(u, edges, bucket, a.nbucket, a.vhalf);
         }
+        Codes<NCHI, NNU> w;
+        w.set(m.chi, nu);
+        w.store(a.codes_n, a.cap, (int64_t)dst);
         if (a.pid_bytes) store_id(a, dst, particle_id<MODE>(a, g, s, (int64_t)start[s] + (i - pre[s]), i - pre[s]));
       } else {
         set_flag(a.flags, FLAG_COUNT);
@@ -1069,8 +1155,6 @@ __global__ __launch_bounds__(NTH) void k_move_scatter_boxes(BoxTable<MoveArgs> t
 template <int NCHI, int NNU, bool SCATTER, bool MEAS>
 __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
   resolve_factors(a);
-  using CT = chi_t<NCHI>;
-  using NT = nu_t<NNU>;
   constexpr int NTH = 1024;
   constexpr int SH = 8 * NCHI - 1;
   // one region holds the potential tile, then the gradient tile computed from it: with the
@@ -1183,8 +1267,6 @@ __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const unsigned long long lt = (1ull << lane) - 1ull;
   const float unit = (float)(1.0 / (double)(1 << SH));
-  CT* chi_n = static_cast<CT*>(a.chi_n);
-  NT* nu_n = static_cast<NT*>(a.nu_n);
   // kick, drift, new cell and code of one particle (cell s at tile offsets (ci, o1, o2), codes chc,
   // nuc); inactive lanes keep v = l = 0
   auto physics = [&](bool active, int s, int ci, int o1, int o2, const int* chc, const int* nuc, float* v, int* k,
@@ -1256,8 +1338,6 @@ __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
   {
     constexpr int NW = NTH / 64;
     const uint32_t tot = pre[TC];
-    const CT* chx = static_cast<const CT*>(a.chi);
-    const NT* nux = static_cast<const NT*>(a.nu);
     int ec = 0;  // the cell of the chunk's first particle (wave-uniform, non-decreasing)
     auto locate = [&](uint32_t c0, int& sc, int64_t& p) {
       while ((uint32_t)__builtin_amdgcn_readfirstlane(pre[ec + 1]) <= c0) ++ec;
@@ -1271,14 +1351,8 @@ __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
       // lanes past the end read the chunk's first particle
       p = i < tot ? (int64_t)start[sc] + (i - pre[sc]) : (int64_t)start[ec] + (c0 - pre[ec]);
     };
-    int chn[3] = {0, 0, 0}, nun[3] = {0, 0, 0};
-    auto load_at = [&](int64_t p) {
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        chn[d] = (int)chx[d * a.cap + p];
-        nun[d] = (int)nux[d * a.cap + p];
-      }
-    };
+    Codes<NCHI, NNU> wn{0u, 0u, 0u, 0u};
+    auto load_at = [&](int64_t p) { wn.load(a.codes, a.cap, p); };
     uint32_t c0 = 64u * (uint32_t)wave;
     int sn = 0;
     int64_t pn = 0;
@@ -1291,7 +1365,9 @@ __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
       const bool active = i < tot;
       const int s = sn;
       const int64_t pc = pn;
-      const int chc[3] = {chn[0], chn[1], chn[2]}, nuc[3] = {nun[0], nun[1], nun[2]};
+      int chc[3], nuc[3];
+      wn.chi(chc);
+      wn.nu(nuc);
       // the codes of the next chunk are requested before this chunk's atomics and stores are issued
       // (past the end the request repeats a particle of this chunk)
       if (c0 + 64u * NW < tot) locate(c0 + 64u * NW, sn, pn);
@@ -1417,12 +1493,15 @@ __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
         if (active) {
           const uint64_t dst = dbase + b0 + rin;
           if (dst < (uint64_t)a.cap) {
+            int nu[3];
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
               const float u = (v[d] - vcn[d]) * inv;
-              nu_n[d * a.cap + dst] = (NT)encode_nu<false>(u, edges, bucket, a.nbucket, a.vhalf);
-              chi_n[d * a.cap + dst] = (CT)cq[d];
+              nu[d] = encode_nu<false>(u, edges, bucket, a.nbucket, a.vhalf);
             }
+            Codes<NCHI, NNU> w;
+            w.set(cq, nu);
+            w.store(a.codes_n, a.cap, (int64_t)dst);
             if (a.pid_bytes) store_id(a, dst, particle_id<0>(a, g, s, pc, 0u));
           } else {
             set_flag(a.flags, FLAG_COUNT);
@@ -1464,16 +1543,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
 // passes. Against recomputing the move, the potential tile (42 to 83 bytes per particle where cells
 // hold few), the interpolation and the kick are gone for 16 bytes per particle written and read:
 // 256^3 particles on 512^3 cells 850 -> 338 us, 512^3 on 512^3 2253 -> 1340 us, for 60 and 110 us
-// more in the count pass. Workgroups of 512 and 1024 threads, and half as many of them on a CU, take
-// the same time: it is bound by the rate of its byte stores, each of which splits into one
-// request per destination line.
+// more in the count pass; 292 and 990 us with the packed codes. Workgroups of 512 and 1024 threads,
+// and half as many of them on a CU, take the same time: it is bound by the requests of its stores
+// (one per destination line) and by its 185 vector instructions a chunk of 64 particles.
 // ---------------------------------------------------------------------------------------------
 constexpr int PLACE_BLK = 256;
 
 template <int NCHI, int NNU, bool PID>
 __device__ __forceinline__ void place_tile(const MoveArgs& a, const unsigned lb) {
-  using CT = chi_t<NCHI>;
-  using NT = nu_t<NNU>;
   constexpr int WC = TC / (PLACE_BLK / 64);  // cells per wavefront
   __shared__ uint32_t next[TC * 27];  // next destination per (own cell, displacement)
   __shared__ uint32_t offr[RC];       // of the tile's and ring's new cells: offset,
@@ -1544,8 +1621,6 @@ __device__ __forceinline__ void place_tile(const MoveArgs& a, const unsigned lb)
   const uint32_t rel = beg - pre;   // storage index of a cell's particle i: rel + i
   const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, WC - 1);
   __syncthreads();
-  CT* const chi_n = static_cast<CT*>(a.chi_n);
-  NT* const nu_n = static_cast<NT*>(a.nu_n);
   int ec = 0;  // the cell of the chunk's first particle
   // cell of each lane's particle of the chunk at c0, its storage index, and the lanes of its cell
   auto locate = [&](uint32_t c0, int& sc, uint32_t& p, unsigned long long& own) {
@@ -1614,17 +1689,13 @@ __device__ __forceinline__ void place_tile(const MoveArgs& a, const unsigned lb)
     if (active && dst >= (uint32_t)a.cap) set_flag(a.flags, FLAG_COUNT);
     dst = min(dst, (uint32_t)a.cap - 1u);
     const float u[3] = {(rc.x - st.x) * st.w, (rc.y - st.y) * st.w, (rc.z - st.z) * st.w};
-    const uint32_t ch[3] = {NCHI == 1 ? w & 255u : r2 & 65535u, NCHI == 1 ? (w >> 8) & 255u : r2 >> 16,
-                            NCHI == 1 ? (w >> 16) & 255u : w & 65535u};
     int nu[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) nu[d] = encode_nu<false>(u[d], edges, bucket, a.nbucket, a.vhalf);
+    Codes<NCHI, NNU> out;
+    out.pack(NCHI == 1 ? w & 0xFFFFFFu : r2, w & 0xFFFFu, nu);
     if (active) {
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        (nu_n + d * a.cap)[dst] = (NT)nu[d];
-        (chi_n + d * a.cap)[dst] = (CT)ch[d];
-      }
+      out.store(a.codes_n, a.cap, (int64_t)dst);
       if constexpr (PID) store_id(a, dst, id);
     }
   };
@@ -1945,26 +2016,58 @@ __global__ void k_load_codes(LoadArgs a) {
 
 template <int NCHI, int NNU>
 __global__ void k_load_encode(const uint32_t* key_sorted, const uint32_t* idx_sorted, const uint16_t* chi_tmp,
-                              const float* v_tmp, int64_t n, void* chi_out, void* nu_out, int64_t cap,
+                              const float* v_tmp, int64_t n, void* codes_out, int64_t cap,
                               const float* vc, const float* vinv, int64_t nc3, const float* edges,
                               const int16_t* bucket, int nbucket, int vhalf, void* pid_out, int pid_bytes) {
-  using CT = chi_t<NCHI>;
-  using NT = nu_t<NNU>;
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n) return;
   const int64_t src = idx_sorted[j];
   const int64_t c = key_sorted[j];
-  CT* co = static_cast<CT*>(chi_out);
-  NT* no = static_cast<NT*>(nu_out);
   const float inv = vinv[c];
+  int ch[3], nu[3];
   for (int d = 0; d < 3; ++d) {
-    co[d * cap + j] = (CT)chi_tmp[d * n + src];
+    ch[d] = (int)chi_tmp[d * n + src];
     const float u = (v_tmp[d * n + src] - vc[d * nc3 + c]) * inv;
-    no[d * cap + j] = (NT)encode_nu<true>(u, edges, bucket, nbucket, vhalf);
+    nu[d] = encode_nu<true>(u, edges, bucket, nbucket, vhalf);
   }
+  Codes<NCHI, NNU> w;
+  w.set(ch, nu);
+  w.store(codes_out, cap, j);
   // the ID of a loaded particle is its index in the input
   if (pid_bytes == 8) static_cast<uint64_t*>(pid_out)[j] = (uint64_t)src;
   else if (pid_bytes == 4) static_cast<uint32_t*>(pid_out)[j] = (uint32_t)src;
+}
+
+// Between the packed words and the checkpoint's planes (chi: 3 planes of n codes, nu: 3 planes of n)
+template <int NCHI, int NNU>
+__global__ __launch_bounds__(256) void k_unpack_codes(const void* codes, int64_t cap, int64_t n, void* chi, void* nu) {
+  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (j >= n) return;
+  Codes<NCHI, NNU> w;
+  w.load(codes, cap, j);
+  int ch[3], nv[3];
+  w.chi(ch);
+  w.nu(nv);
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    static_cast<chi_t<NCHI>*>(chi)[d * n + j] = (chi_t<NCHI>)ch[d];
+    static_cast<nu_t<NNU>*>(nu)[d * n + j] = (nu_t<NNU>)nv[d];
+  }
+}
+
+template <int NCHI, int NNU>
+__global__ __launch_bounds__(256) void k_pack_codes(const void* chi, const void* nu, int64_t n, void* codes, int64_t cap) {
+  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (j >= n) return;
+  int ch[3], nv[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    ch[d] = (int)static_cast<const chi_t<NCHI>*>(chi)[d * n + j];
+    nv[d] = (int)static_cast<const nu_t<NNU>*>(nu)[d * n + j];
+  }
+  Codes<NCHI, NNU> w;
+  w.set(ch, nv);
+  w.store(codes, cap, j);
 }
 
 // IDs 0 .. n-1 in storage order
@@ -2027,7 +2130,7 @@ __global__ void k_noise(float* out, int n, int64_t pitch_f, uint64_t seed) {
 // the deposit's arguments for the state of parity cur, and its grid (columns x z chunks)
 static DepArgs deposit_args(const Sim& s, int cur, dim3* grid) {
   DepArgs a;
-  a.chi = s.chi[cur];
+  a.codes = s.codes[cur];
   a.cnt = s.cnt[cur];
   a.off = s.off[cur];
   a.cap = s.capacity;
@@ -2141,14 +2244,12 @@ static bool use_records(const Sim& s) { return s.rec && s.turn_limit == kTurnLim
 static MoveArgs move_args(const Sim& s, int cur, float kfac, float dfac, bool dev_sched) {
   const int nxt = cur ^ 1;
   MoveArgs a{};
-  a.chi = s.chi[cur];
-  a.nu = s.nu[cur];
+  a.codes = s.codes[cur];
   a.cnt = s.cnt[cur];
   a.off = s.off[cur];
   a.vc = s.vc[cur];
   a.vs = s.vs[cur];
-  a.chi_n = s.chi[nxt];
-  a.nu_n = s.nu[nxt];
+  a.codes_n = s.codes[nxt];
   a.off_n = s.off[nxt];
   a.vc_n = s.vc[nxt];
   a.vinv = s.vinv;
@@ -2449,8 +2550,8 @@ void launch_load(Sim& s, const double* dx, const float* /*unused*/, int64_t n, h
   sort_pairs_by_key(s, key, idx, key2, idx2, n, (uint32_t)(s.nc3 - 1), st, &ks, &is);
   link_scan_finalize(s, nxt, s.cnt[nxt], st);
 #define CUBE_ENC(X, V)                                                                                       \
-  k_load_encode<X, V><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(ks, is, chi_tmp, v_tmp, n, s.chi[nxt],    \
-                                                                   s.nu[nxt], s.capacity, s.vc[nxt], s.vinv, \
+  k_load_encode<X, V><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(ks, is, chi_tmp, v_tmp, n, s.codes[nxt],  \
+                                                                   s.capacity, s.vc[nxt], s.vinv, \
                                                                    s.nc3, s.tedge, s.tbucket, s.nbucket, (s.vm - 1) / 2, \
                                                                    s.pid[nxt], s.pid_bytes)
   if (n > 0) {
@@ -2465,6 +2566,37 @@ void launch_load(Sim& s, const double* dx, const float* /*unused*/, int64_t n, h
   s.cur = nxt;
 }
 
+// where the checkpoint's planes are staged: in the other state buffer (scratch between steps), the
+// wider codes first so that each plane is aligned to its code
+void staged_planes(const Sim& s, void** chi, void** nu) {
+  char* const w = static_cast<char*>(s.codes[s.cur ^ 1]);
+  const bool chi_first = s.nchi >= s.nnu;
+  *chi = chi_first ? w : w + (size_t)3 * s.n * s.nnu;
+  *nu = chi_first ? w + (size_t)3 * s.n * s.nchi : w;
+}
+
+void launch_unpack_codes(Sim& s, hipStream_t st) {
+  if (s.n == 0) return;
+  void *chi, *nu;
+  staged_planes(s, &chi, &nu);
+#define CUBE_UNPACK(X, V) \
+  k_unpack_codes<X, V><<<(unsigned)((s.n + 255) / 256), 256, 0, st>>>(s.codes[s.cur], s.capacity, s.n, chi, nu)
+  CUBE_XV_DISPATCH(s.nchi, s.nnu, CUBE_UNPACK);
+#undef CUBE_UNPACK
+  CUBE_HIP(hipGetLastError());
+}
+
+void launch_pack_codes(Sim& s, hipStream_t st) {
+  if (s.n == 0) return;
+  void *chi, *nu;
+  staged_planes(s, &chi, &nu);
+#define CUBE_PACK(X, V) \
+  k_pack_codes<X, V><<<(unsigned)((s.n + 255) / 256), 256, 0, st>>>(chi, nu, s.n, s.codes[s.cur], s.capacity)
+  CUBE_XV_DISPATCH(s.nchi, s.nnu, CUBE_PACK);
+#undef CUBE_PACK
+  CUBE_HIP(hipGetLastError());
+}
+
 void launch_pid_iota(Sim& s, hipStream_t st) {
   if (!s.pid_bytes || s.n == 0) return;
   k_pid_iota<<<(unsigned)((s.n + 255) / 256), 256, 0, st>>>(s.pid[s.cur], s.pid_bytes, s.n);
@@ -2473,10 +2605,9 @@ void launch_pid_iota(Sim& s, hipStream_t st) {
 
 // largest |v|^2 of the decoded state (the velocity bound of the first adaptive steps): one thread
 // per particle, its cell found by bisection in the cell offsets
-template <int NNU>
-__global__ void k_state_speed(const void* nu, const uint64_t* off, const float* vc, const float* vs,
+template <int NCHI, int NNU>
+__global__ void k_state_speed(const void* codes, const uint64_t* off, const float* vc, const float* vs,
                               const float* tdec, int64_t n, int64_t cap, int64_t nc3, int vhalf, uint32_t* out) {
-  using NT = nu_t<NNU>;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   float vv = 0.0f;
   if (i < n) {
@@ -2486,11 +2617,14 @@ __global__ void k_state_speed(const void* nu, const uint64_t* off, const float* 
       if (off[mid] <= (uint64_t)i) lo = mid;
       else hi = mid;
     }
-    const NT* nv = static_cast<const NT*>(nu);
+    Codes<NCHI, NNU> w;
+    w.load(codes, cap, i);
+    int nv[3];
+    w.nu(nv);
     float v[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-      int c = (int)nv[d * cap + i];
+      int c = nv[d];
       c = c < -vhalf ? -vhalf : (c > vhalf ? vhalf : c);
       v[d] = __builtin_fmaf(vs[lo], tdec[c + vhalf], vc[d * nc3 + lo]);
     }
@@ -2506,12 +2640,11 @@ float launch_state_speed2(Sim& s, hipStream_t st) {
   if (s.n > 0) {
     const unsigned grid = (unsigned)((s.n + 255) / 256);
     const int vh = (s.vm - 1) / 2;
-    if (s.nnu == 1)
-      k_state_speed<1><<<grid, 256, 0, st>>>(s.nu[s.cur], s.off[s.cur], s.vc[s.cur], s.vs[s.cur], s.tdec, s.n,
-                                             s.capacity, s.nc3, vh, s.amax);
-    else
-      k_state_speed<2><<<grid, 256, 0, st>>>(s.nu[s.cur], s.off[s.cur], s.vc[s.cur], s.vs[s.cur], s.tdec, s.n,
-                                             s.capacity, s.nc3, vh, s.amax);
+#define CUBE_SPEED(X, V)                                                                                              \
+  k_state_speed<X, V><<<grid, 256, 0, st>>>(s.codes[s.cur], s.off[s.cur], s.vc[s.cur], s.vs[s.cur], s.tdec, s.n,         \
+                                            s.capacity, s.nc3, vh, s.amax)
+    CUBE_XV_DISPATCH(s.nchi, s.nnu, CUBE_SPEED);
+#undef CUBE_SPEED
     CUBE_HIP(hipGetLastError());
   }
   uint32_t bits = 0;
