@@ -252,9 +252,7 @@ void check_flags(Sim& s) {
   std::vector<Sim::PhaseRec> log;
   log.swap(s.phases);
   if (!f[0]) return;
-  // a link pass that returned early has left the count pass's sums in the moment accumulators
   CUBE_HIP(hipMemsetAsync(s.flags, 0, 2 * sizeof(uint32_t), s.stream));
-  CUBE_HIP(hipMemsetAsync(s.mom, 0, sizeof(int64_t) * 4 * s.nc3, s.stream));
   CUBE_HIP(hipStreamSynchronize(s.stream));
   // the failing phase and every later one were not applied: back to the state before it
   std::string where;
@@ -430,7 +428,7 @@ int64_t footprint_bytes(const cube_params& p) {
   const int64_t pb = 3 * cap * (p.x_bytes + p.v_bytes);
   auto field = [](int64_t n) { return n * n * (n / 2 + (n >= 1024 ? 8 : 16)) * 2 * (int64_t)sizeof(float); };
   int64_t b = 2 * (pb + 4 * nc3 + 8 * (nc3 + 1) + 12 * nc3 + 4 * nc3);  // state, double buffered
-  b += 4 * nc3 + 2 * 108 * nc3 + 32 * nc3 + 8 * nc3;                  // vinv, mig and as much spare, mom, dev
+  b += 4 * nc3 + 2 * 108 * nc3 + 32 * nc3 + 8 * nc3;                  // vinv, mig, mom (and 32 nc3 to spare), dev
   b += 24 * ((nc3 + 255) / 256) + 64 + 16 + 40 * (nm / 2 + 1);       // link blocks, scalars, flags, P(k)
   b += 12 * nm + (np != nm ? 12 * np : 0) + field(nm);               // FFT plans and the mesh
   const int64_t m = ((int64_t)1 << (8 * p.v_bytes)) - 1;
@@ -522,7 +520,7 @@ int cube_create(const cube_params* params, void* stream, const cube_allocator* a
     }
     s.vinv = static_cast<float*>(s.dmalloc(sizeof(float) * s.nc3));
     s.mig = static_cast<uint32_t*>(s.dmalloc(sizeof(uint32_t) * 27 * s.nc3));
-    s.mom = static_cast<int64_t*>(s.dmalloc(sizeof(int64_t) * 4 * s.nc3));
+    s.mom = static_cast<int64_t*>(s.dmalloc((size_t)(s.nc3 / 64) * 216 * 4 * sizeof(int64_t)));
     s.dev = static_cast<double*>(s.dmalloc(sizeof(double) * s.nc3));
     s.nblk = (s.nc3 + 255) / 256;
     s.blk_n = static_cast<uint64_t*>(s.dmalloc(sizeof(uint64_t) * s.nblk));
@@ -549,7 +547,6 @@ int cube_create(const cube_params* params, void* stream, const cube_allocator* a
       CUBE_HIP(hipMemcpy(s.sched_dev, kd.data(), sizeof(float) * kd.size(), hipMemcpyHostToDevice));
       CUBE_HIP(hipMemsetAsync(s.step_dev, 0, sizeof(int) * 4, s.stream));
     }
-    CUBE_HIP(hipMemsetAsync(s.mom, 0, sizeof(int64_t) * 4 * s.nc3, s.stream));
     CUBE_HIP(hipMemsetAsync(s.flags, 0, sizeof(uint32_t) * 4, s.stream));
     CUBE_HIP(hipMemsetAsync(s.mesh, 0, s.mesh_plan.field_floats() * sizeof(float), s.stream));
     CUBE_HIP(hipStreamSynchronize(s.stream));

@@ -249,33 +249,32 @@ void autotune_sim(Sim& s) {
   set_z_layout(s, best_l == 0 && !had_scratch ? -1 : best_l);
   launch_deposit(s, s.stream);
   solve_potential(s, s.stream);
-  // move passes: per-corner gradient vs precomputed gradient tile, each pass timed on its own
-  // (events around the count and the scatter pass), with this step's factors
+  // move: the count pass and the scatter from records have one kernel each; the recomputing scatter
+  // (no room for the records) has two, per-corner gradient and gradient tile, timed by the events around
+  // it with this step's factors
   ensure_records(s);
   const int j = std::min(s.steps_done, s.p.n_steps - 1);
   const float kf = (float)(-s.kicks[j] / 12.0), df = (float)s.drifts[j];
-  float tc[2] = {0.f, 0.f}, ts[2] = {0.f, 0.f};
+  float tc = 0.f, ts[2] = {0.f, 0.f};
   hipEvent_t* me = s.ev + 8;  // four events: before count, after count, after link, after scatter
-  for (int v = 0; v <= 1; ++v) {
-    s.move_variant = v;
+  const int tried = s.rec ? 1 : 2;
+  for (int v = 0; v < tried; ++v) {
+    s.move_variant = v ? 2 : 0;
     for (int r = 0; r <= reps; ++r) {
       const int cur = s.cur;
       launch_move(s, 0, kf, df, nullptr, 0.0f, s.stream, me);
       s.cur = cur;  // discard the result
       const float c = elapsed_ms(me[0], me[1]), sc = elapsed_ms(me[2], me[3]);
       if (r > 0) {
-        tc[v] += c;
+        tc += v == 0 ? c : 0.0f;
         ts[v] += sc;
       }
     }
   }
-  for (int v = 0; v <= 1; ++v) {
-    note("count " + std::to_string(v), tc[v]);
-    note("scatter " + std::to_string(v), ts[v]);
-  }
+  note("count", tc);
+  for (int v = 0; v < tried; ++v) note("scatter " + std::to_string(v), ts[v]);
   s.autotune_report = rep;
-  const bool tcnt = tc[1] < tc[0], tsct = ts[1] < ts[0];
-  s.move_variant = tcnt ? (tsct ? 1 : 3) : (tsct ? 2 : 0);
+  s.move_variant = tried == 2 && ts[1] < ts[0] ? 2 : 0;
   // a timed move may have raised a flag that the real step will raise again; clear it here
   CUBE_HIP(hipMemsetAsync(s.flags, 0, sizeof(uint32_t), s.stream));
   CUBE_HIP(hipStreamSynchronize(s.stream));

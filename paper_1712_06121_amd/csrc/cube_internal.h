@@ -131,7 +131,8 @@ struct Sim {
   // move scratch
   float* vinv = nullptr;       // nc3 encode scale 1/(sigma sqrt(2/pi))
   uint32_t* mig = nullptr;     // 27 x nc3 counts per (displacement, source cell); the link turns them into slots
-  int64_t* mom = nullptr;      // 4 x nc3: S1x, S1y, S1z, S2
+  int64_t* mom = nullptr;      // S1x, S1y, S1z, S2 per cell of every tile of 4^3 cells and its ring (6^3);
+                               // load path: 4 planes of nc3
   double* dev = nullptr;       // nc3 3-D velocity variance per cell
   uint64_t* blk_n = nullptr;   // per link block: count
   int64_t* blk_q = nullptr;    // per link block: dispersion sum

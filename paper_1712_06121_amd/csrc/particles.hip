@@ -493,7 +493,7 @@ struct MoveArgs {
   int nbucket;
   int vhalf;
   uint32_t* mig;  // per (displacement, source cell): counts after the count pass, slots after the link
-  int64_t* mom;
+  int64_t* mom;   // count pass: four moments per cell of a tile and its ring, a block per tile
   uint32_t* flags;
   // initial conditions
   const float* psi0;
@@ -531,16 +531,6 @@ __device__ __forceinline__ float wave_max(float x) {
 
 __global__ void k_clear_u32(uint32_t* p, int n) {
   if ((int)threadIdx.x < n) p[threadIdx.x] = 0u;
-}
-
-// the wave's largest |v|^2 and |t|^2 into the step maxima (non-negative floats order as their bits)
-__device__ __forceinline__ void raise_maxima(uint32_t* amax, float vv, float tq) {
-  vv = wave_max(vv);
-  tq = wave_max(tq);
-  if ((threadIdx.x & 63) == 0) {
-    if (vv > 0.0f) atomicMax(&amax[0], __float_as_uint(vv));
-    if (tq > 0.0f) atomicMax(&amax[1], __float_as_uint(tq));
-  }
 }
 
 // the ID of the particle at storage index p (steps), or of lattice particle li of tile cell s
@@ -619,7 +609,6 @@ struct Moved {
   int k[3];
   int chi[3];
   bool ok;
-  float vv, tq;  // |v|^2 after the kick and |t|^2 of the interpolated gradient (step passes)
 };
 
 constexpr int DG = F + 2;  // precomputed-gradient tile side: fine cells -1 .. F of the tile
@@ -679,16 +668,14 @@ __device__ __forceinline__ bool new_cell(float ln, float vd, uint32_t* flags, in
   return ok;
 }
 
-template <int NCHI, int NNU, int MODE, bool PRE, bool MEAS = false>
-__device__ __forceinline__ Moved move_particle(const MoveArgs& a, const float* ph, const float* gd, int s, int64_t p,
+template <int NCHI, int NNU, int MODE>
+__device__ __forceinline__ Moved move_particle(const MoveArgs& a, const float* ph, int s, int64_t p,
                                                uint32_t li, const TileGeom& g) {
   constexpr int SH = 8 * NCHI - 1;
   const int o[3] = {s % T, (s / T) % T, s / (T * T)};
   const int64_t c = (g.cx0 + o[0]) + (int64_t)a.nc * ((g.cy0 + o[1]) + (int64_t)a.nc * (g.cz0 + o[2]));
   float l[3], v[3];
   Moved m;
-  m.vv = 0.0f;
-  m.tq = 0.0f;
   if constexpr (MODE == 2) {
     const int lat[3] = {(int)(li % a.q), (int)((li / a.q) % a.q), (int)(li / (a.q * a.q))};
     const int64_t gx = (int64_t)(g.cx0 + o[0]) * a.q + lat[0];
@@ -737,17 +724,15 @@ __device__ __forceinline__ Moved move_particle(const MoveArgs& a, const float* p
           float racc[2];
 #pragma unroll
           for (int cy = 0; cy < 2; ++cy) {
-            const float d0 = grad_at<PRE>(ph, gd, d, i0[0], i0[1] + cy, i0[2] + cz);
-            const float d1 = grad_at<PRE>(ph, gd, d, i0[0] + 1, i0[1] + cy, i0[2] + cz);
+            const float d0 = grad_at<false>(ph, nullptr, d, i0[0], i0[1] + cy, i0[2] + cz);
+            const float d1 = grad_at<false>(ph, nullptr, d, i0[0] + 1, i0[1] + cy, i0[2] + cz);
             racc[cy] = __builtin_fmaf(w1[0], d1, w0[0] * d0);
           }
           sacc[cz] = __builtin_fmaf(w1[1], racc[1], w0[1] * racc[0]);
         }
         const float t = __builtin_fmaf(w1[2], sacc[1], w0[2] * sacc[0]);
         v[d] = __builtin_fmaf(t, a.kf, v[d]);
-        if constexpr (MEAS) m.tq = d == 0 ? t * t : m.tq + t * t;
       }
-      if constexpr (MEAS) m.vv = (v[0] * v[0] + v[1] * v[1]) + v[2] * v[2];
     }
 #pragma unroll
     for (int d = 0; d < 3; ++d) l[d] = __builtin_fmaf(v[d], a.df, l[d]);
@@ -767,8 +752,8 @@ __device__ __forceinline__ Moved move_particle(const MoveArgs& a, const float* p
 // Potential tile (fine cells -3 .. F+2 of the tile, wrapped) and, with PRE, the unnormalised
 // 4-point gradient of every corner cell -1 .. F. The gradient uses the same IEEE operations as the
 // per-corner evaluation, so both paths give identical bits.
-template <int MODE, bool PRE, int NTH>
-__device__ __forceinline__ void load_potential(const MoveArgs& a, float* ph, float* gd, const TileGeom& g) {
+template <int MODE, int NTH>
+__device__ __forceinline__ void load_potential(const MoveArgs& a, float* ph, const TileGeom& g) {
   if constexpr (MODE == 0) {
     const int fx0 = g.cx0 * 4 - 3, fy0 = g.cy0 * 4 - 3, fz0 = g.cz0 * 4 - 3;
     const int64_t plane = (int64_t)a.nm * a.pitch_f;
@@ -818,18 +803,6 @@ __device__ __forceinline__ void load_potential(const MoveArgs& a, float* ph, flo
         if (x < PH && r < PH * PH) ph[r * PH + x] = stage[k];
       }
     }
-    if constexpr (PRE) {
-      __syncthreads();
-      const int hw = threadIdx.x >> 5, x = threadIdx.x & 31;
-      for (int r = hw; r < DG * DG; r += NTH / 32) {
-        if (x < DG) {
-          const int z = r / DG, y = r - z * DG;
-          const int i = r * DG + x;
-#pragma unroll
-          for (int d = 0; d < 3; ++d) gd[d * DG * DG * DG + i] = grad_at<false>(ph, gd, d, x - 1, y - 1, z - 1);
-        }
-      }
-    }
   }
 }
 
@@ -877,149 +850,330 @@ __device__ __forceinline__ int find_cell_in(const uint32_t* pre, int lo, int hi,
   return lo;
 }
 
-// The tile's per (own cell, displacement) counts (LDS, [cell][27]) to mig[d][cell]: a wavefront
-// writes one displacement of all 64 own cells, a lane per cell, so the array offset is uniform.
-template <int NTH>
-__device__ __forceinline__ void flush_counts(const MoveArgs& a, const TileGeom& g, const uint32_t* cnt) {
-  static_assert(TC == 64 && NTH % 64 == 0, "one lane per own cell");
-  const int s = threadIdx.x & 63;
-  uint32_t* const col = a.mig + (g.cx0 + (int64_t)a.nc * (g.cy0 + (int64_t)a.nc * g.cz0)) + s % T +
-                        (int64_t)a.nc * ((s / T) % T) + (int64_t)a.nc * a.nc * (s / (T * T));
-  for (int d = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); d < 27; d += NTH / 64) col[d * a.nc3] = cnt[s * 27 + d];
-}
 
-template <int MODE, bool PRE>
-struct MoveLds {
-  static constexpr int kPh = MODE == 0 ? PH * PH * PH : 1;
-  static constexpr int kGd = (MODE == 0 && PRE) ? 3 * DG * DG * DG : 1;
-  // moments: in LDS over the tile and its ring, flushed at the end; with the potential tile in LDS
-  // (MODE 0) they go to the global accumulators directly, so that three workgroups fit a CU
-  static constexpr bool kGlobalMom = MODE == 0;
-  static constexpr int kMom = kGlobalMom ? TC * 4 : RC * 4;  // own cells only, or tile and ring
-};
+// ---------------------------------------------------------------------------------------------
+// Count pass: every particle's kick, drift, new cell and codes, the counts per (source cell,
+// displacement) and the fixed-point velocity moments of the new cells. MODE 0: step; 1: drift only;
+// 2: initial conditions.
+//
+// One workgroup per tile of 4^3 coarse cells. The wavefronts take every NW-th chunk of 64 of the
+// tile's particles, its cells one after the other in storage order, so that a crowded cell is shared
+// by all of them and few particles in a cell leave no lanes idle; nothing here depends on the order.
+// The moments of stayers go to CCOPY copies per cell of the LDS accumulators, a lane to copy
+// lane % CCOPY: an LDS add takes 2 cycles per lane on one address (128 for a wavefront inside one
+// cell), 16 with eight copies, on a pipe beside the vector ALU. Particles that leave their cell add to
+// one accumulator per cell of the tile and its ring. A tile writes all its sums to its own block of the
+// moment table, and the link adds up the (at most eight) blocks that can reach a cell: no device atomics.
+// Stayers are not counted at all (the cell's particles less those that leave).
+//
+// The potential tile (fine cells -4 .. 19 along x, -3 .. 18 along y and z) is loaded and kept in quads
+// of four floats along x, which never straddle the box's edge. Its plane pitch of 540 floats spreads
+// the stencils of a cell's particles over the LDS banks (8.0 cycles a read of 64 lanes on average
+// over uniform positions; 9.6 with 528).
+//
+// Two workgroups of 16 wavefronts share a CU (64 VGPRs; workgroups of 8 and 12 take 3 to 12% longer
+// where cells hold many particles). Before (512 threads, moments by wavefront prefix scans and device
+// atomics) and now: 512^3 particles on 512^3 cells 2291 -> 1647 us early, 2838 -> 1750 clustered, 374 vector
+// instructions per 64 particles where there were 535 to 582; 256^3 on 512^3 cells 871 -> 692 us, bound by
+// the latencies of the tile's set-up and flush; with step maxima, 96^3 on 128^3, 392 -> 28 us (an atomic
+// pair on one address per 64 particles before, one per tile now).
+// ---------------------------------------------------------------------------------------------
+constexpr int CNTH = 1024;       // threads per workgroup
+constexpr int CCOPY = 8;         // copies of an own cell's moment accumulators
+constexpr int CPX = F + 8;       // potential row in LDS: 24 floats
+constexpr int CPP = PH * CPX + 12;  // potential plane in LDS
+constexpr int CSLOT = TC * CCOPY + RC;  // accumulators per moment: own cells' copies, then tile and ring
 
-// count pass over one tile (logical block lb of the box)
-template <int NCHI, int NNU, int MODE, bool PRE, int NTH, bool MEAS>
-__device__ __forceinline__ void move_count_tile(MoveArgs a, const unsigned lb) {
+template <int NCHI, int NNU, int MODE, bool MEAS>
+__device__ __forceinline__ void count_tile(MoveArgs a, const unsigned lb) {
   resolve_factors(a);
-  using L = MoveLds<MODE, PRE>;
-  __shared__ float ph[L::kPh];
-  __shared__ float gd[L::kGd];
-  __shared__ uint32_t mcnt[TC * 27];
-  __shared__ unsigned long long mom[L::kMom];
-  __shared__ uint32_t pre[TC + 1];
-  __shared__ uint64_t start[TC];
-  __shared__ uint32_t wsum[NTH / 64];
-  const TileGeom g = tile_of(lb, a.nt);
-  load_potential<MODE, PRE, NTH>(a, ph, gd, g);
-  for (int i = threadIdx.x; i < TC * 27; i += NTH) mcnt[i] = 0u;
-  for (int i = threadIdx.x; i < L::kMom; i += NTH) mom[i] = 0ull;
-  const uint32_t total = own_cells<MODE>(a, g, pre, start, wsum);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int c0, c1;
-  wave_cells(pre, total, wave, NTH / 64, c0, c1);
-  const uint32_t p0 = pre[c0], p1 = pre[c1];
-  for (uint32_t base = p0; base < p1; base += 64) {
-    const uint32_t i = base + lane;
-    const bool active = i < p1;  // active lanes form a prefix of the wave
-    int key = -1, r = 0;
-    long long q[4];
-    float vm[3] = {0.f, 0.f, 0.f};
-    float vv = 0.f, tq = 0.f;
-    if (active) {
-      const int s = find_cell_in(pre, c0, c1, i);
-      const uint32_t li = i - pre[s];
-      const int64_t p = (int64_t)start[s] + li;
-      const Moved m = move_particle<NCHI, NNU, MODE, PRE, MEAS>(a, ph, gd, s, p, li, g);
-      const int dcode = (m.k[2] + 1) * 9 + (m.k[1] + 1) * 3 + (m.k[0] + 1);
-      key = s * 27 + dcode;
-      if constexpr (MODE != 2)
-        if (a.rec) store_record<NCHI>(a, p, m.v, m.chi, dcode);
-      r = (s % T + 1 + m.k[0]) + RG * ((s / T) % T + 1 + m.k[1]) + RG * RG * (s / (T * T) + 1 + m.k[2]);
-      vm[0] = m.v[0];
-      vm[1] = m.v[1];
-      vm[2] = m.v[2];
-      vv = m.vv;
-      tq = m.tq;
-    }
-    if constexpr (MEAS) raise_maxima(a.amax, vv, tq);
-    velocity_moments(vm, q);
-    // sum over runs of consecutive lanes with the same (cell, displacement): most particles stay
-    // in their cell, so one atomic per run replaces up to 64 conflicting ones
-    const int kprev = __shfl_up(key, 1, 64);
-    const bool head = lane == 0 || kprev != key;
-    // st: the first lane of this lane's run, the highest run head at or below it (lane 0 is one)
-    const unsigned long long heads = __ballot(head);
-    const int st = 63 - __clzll(heads & (lane == 63 ? ~0ull : ((2ull << lane) - 1ull)));
-    // run sums from one prefix scan: the scan at the lane minus the scan before the run
+  constexpr int SH = 8 * NCHI - 1;
+  constexpr int NW = CNTH / 64;
+  __shared__ __align__(16) float ph[MODE == 0 ? PH * CPP : 4];
+  __shared__ __align__(16) unsigned long long mom[4 * CSLOT];
+  __shared__ __align__(16) uint32_t left[TC * 27];  // particles leaving own cell s with displacement d (not 13)
+  __shared__ float4 cellv[TC];                      // mean velocity and decode scale of the own cells
+  __shared__ float tdec_lds[NNU == 1 ? 255 : 1];
+  __shared__ uint32_t top[2];
+  const TileGeom g = tile_of((int)lb, a.nt);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // own cell `lane`, in every wavefront: count and storage start
+  int ox, oy, oz;
+  tile_xyz(lane, ox, oy, oz);
+  const uint32_t oc = (uint32_t)(g.cx0 + ox) + (uint32_t)a.nc * ((uint32_t)(g.cy0 + oy) + (uint32_t)a.nc * (uint32_t)(g.cz0 + oz));
+  uint32_t cnt;
+  uint64_t beg = 0;  // initial conditions: the lattice particles of a cell are numbered from 0
+  if constexpr (MODE == 2) {
+    cnt = (uint32_t)(a.q * a.q * a.q);
+  } else {
+    cnt = a.cnt[oc];
+    beg = a.off[oc];
+  }
+  float tdec_r = 0.0f;
+  float4 cv_r = make_float4(0.f, 0.f, 0.f, 0.f);
+  if constexpr (MODE != 2) {
+    if (NNU == 1 && threadIdx.x < 255) tdec_r = a.tdec[threadIdx.x];
+    if (threadIdx.x < TC) cv_r = make_float4(a.vc[oc], (a.vc + a.nc3)[oc], (a.vc + 2 * a.nc3)[oc], a.vs[oc]);
+  }
+  if constexpr (MODE == 0) {
+    // every load of the tile in flight at once; z and y wrap only in the tiles at the box's faces
+    constexpr uint32_t QX = CPX / 4, NQ = PH * PH * QX, NL = (NQ + CNTH - 1) / CNTH;
+    typedef float quad __attribute__((ext_vector_type(4)));  // (an array of float4 goes to scratch memory here)
+    quad stage[NL];
+    const int fx0 = 4 * (g.cx0 - 1), fy0 = 4 * g.cy0 - 3, fz0 = 4 * g.cz0 - 3;
+    const bool inner = fx0 >= 0 && fy0 >= 0 && fz0 >= 0 && fx0 + CPX <= a.nm && fy0 + PH <= a.nm && fz0 + PH <= a.nm;
+    const uint32_t nmu = (uint32_t)a.nm, pitch = (uint32_t)a.pitch_f;
+    if (inner) {
+      const float* const src = a.mesh + ((int64_t)fz0 * nmu + fy0) * pitch + fx0;
 #pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      const unsigned long long ps = wave_scan_u64((unsigned long long)q[d]);
-      const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)ps, st - 1, 64);
-      const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(ps >> 32), st - 1, 64);
-      const unsigned long long before = st > 0 ? (((unsigned long long)hi << 32) | lo) : 0ull;
-      q[d] = (long long)(ps - before);
-    }
-    const int knext = __shfl_down(key, 1, 64);
-    const bool tail = lane == 63 || knext != key;
-    if (active && tail) {
-      atomicAdd(&mcnt[key], (uint32_t)(lane - st + 1));
-      if constexpr (L::kGlobalMom) {
-        // new cell inside the tile: the tile's LDS accumulators; in the ring: the global ones
-        const int rx = r % RG, ry = (r / RG) % RG, rz = r / (RG * RG);
-        if (rx >= 1 && rx <= T && ry >= 1 && ry <= T && rz >= 1 && rz <= T) {
-          const int so = (rx - 1) + T * ((ry - 1) + T * (rz - 1));
-#pragma unroll
-          for (int d = 0; d < 4; ++d) atomicAdd(&mom[so * 4 + d], (unsigned long long)q[d]);
-        } else {
-          const int gx = wrapi(g.cx0 - 1 + rx, a.nc), gy = wrapi(g.cy0 - 1 + ry, a.nc);
-          const int gz = wrapi(g.cz0 - 1 + rz, a.nc);
-          const int64_t cn = gx + (int64_t)a.nc * (gy + (int64_t)a.nc * gz);
-#pragma unroll
-          for (int d = 0; d < 4; ++d)
-            atomicAdd(reinterpret_cast<unsigned long long*>(&a.mom[d * a.nc3 + cn]), (unsigned long long)q[d]);
+      for (uint32_t k = 0; k < NL; ++k) {
+        const uint32_t e = threadIdx.x + k * CNTH;
+        if (e < NQ) {
+          // 22 planes of at most 2048 rows of 2064 floats: below 2^27 floats from the first
+          const uint32_t r = e / QX, j = e - r * QX, z = r / PH, y = r - z * PH;
+          stage[k] = *reinterpret_cast<const quad*>(src + (__umul24(__umul24(z, nmu) + y, pitch) + 4u * j));
         }
-      } else {
-#pragma unroll
-        for (int d = 0; d < 4; ++d) atomicAdd(&mom[r * 4 + d], (unsigned long long)q[d]);
       }
+    } else {
+#pragma unroll
+      for (uint32_t k = 0; k < NL; ++k) {
+        const uint32_t e = threadIdx.x + k * CNTH;
+        if (e < NQ) {
+          const uint32_t r = e / QX, j = e - r * QX, z = r / PH, y = r - z * PH;
+          const int gx = wrapi(fx0 + 4 * (int)j, a.nm), gy = wrapi(fy0 + (int)y, a.nm), gz = wrapi(fz0 + (int)z, a.nm);
+          stage[k] = *reinterpret_cast<const quad*>(a.mesh + ((int64_t)gz * a.nm + gy) * a.pitch_f + gx);
+        }
+      }
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < NL; ++k) {
+      const uint32_t e = threadIdx.x + k * CNTH;
+      if (e < NQ) *reinterpret_cast<quad*>(&ph[4 * e + (CPP - PH * CPX) * (e / (PH * QX))]) = stage[k];
+    }
+  }
+  if constexpr (MODE != 2) {
+    if (NNU == 1 && threadIdx.x < 255) tdec_lds[threadIdx.x] = tdec_r;
+    if (threadIdx.x < TC) cellv[threadIdx.x] = cv_r;
+  }
+  for (int i = threadIdx.x; i < 2 * CSLOT; i += CNTH) reinterpret_cast<uint4*>(mom)[i] = make_uint4(0u, 0u, 0u, 0u);
+  for (int i = threadIdx.x; i < TC * 27 / 4; i += CNTH) reinterpret_cast<uint4*>(left)[i] = make_uint4(0u, 0u, 0u, 0u);
+  if (threadIdx.x < 2) top[threadIdx.x] = 0u;
+  // inclusive prefix of the counts over the own cells, in the lanes of every wavefront
+  const uint32_t inc = (uint32_t)wave_scan_u64(cnt);
+  const uint64_t rel = beg - (inc - cnt);  // storage index of a cell's particle i of the tile: rel + i
+  const uint32_t rel_lo = (uint32_t)rel, rel_hi = (uint32_t)(rel >> 32);
+  const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+  __syncthreads();
+  const float* const tdec = NNU == 1 ? tdec_lds : a.tdec;
+  const float unit = (float)(1.0 / (double)(1 << SH));
+
+  // cell and storage index of each lane's particle of the chunk at c0 (lanes past the end: the tile's
+  // last particle)
+  auto locate = [&](uint32_t c0, int& sc, int64_t& p) {
+    int q = __popcll(__ballot(inc <= c0));  // the cell of the chunk's first particle
+    uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)inc, q);
+    const uint32_t i = min(c0 + (uint32_t)lane, tot - 1u);
+    sc = q;
+    uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)rel_lo, q), hi = (uint32_t)__builtin_amdgcn_readlane((int)rel_hi, q);
+    const uint32_t stop = min(c0 + 64u, tot);
+    while (end < stop) {
+      const uint32_t b = end;  // first particle of the next cell
+      ++q;
+      end = (uint32_t)__builtin_amdgcn_readlane((int)inc, q);
+      const uint32_t ql = (uint32_t)__builtin_amdgcn_readlane((int)rel_lo, q), qh = (uint32_t)__builtin_amdgcn_readlane((int)rel_hi, q);
+      if (i >= b) {
+        sc = q;
+        lo = ql;
+        hi = qh;
+      }
+    }
+    p = (int64_t)((((uint64_t)hi << 32) | lo) + i);
+  };
+
+  float vmax = 0.0f, gmax = 0.0f;  // largest |v|^2 and |t|^2 of this lane's particles
+  Codes<NCHI, NNU> wn{0u, 0u, 0u, 0u};
+  int sn = 0;
+  int64_t pn = 0;
+  auto chunk = [&](auto full, uint32_t c0) {
+    constexpr bool FULL = decltype(full)::value;
+    const int s = sn;
+    const int64_t pc = pn;
+    int ch[3], nuc[3];
+    if constexpr (MODE != 2) {
+      wn.chi(ch);
+      wn.nu(nuc);
+    }
+    // the codes of the wavefront's next chunk are requested before this one's record is stored (past
+    // the end the request repeats a particle of this chunk)
+    if (c0 + 64u * NW < tot) locate(c0 + 64u * NW, sn, pn);
+    if constexpr (MODE != 2) wn.load(a.codes, a.cap, pn);
+    const bool active = FULL || c0 + (uint32_t)lane < tot;
+    int o[3];
+    tile_xyz(s, o[0], o[1], o[2]);
+    float v[3], l[3];
+    if constexpr (MODE == 2) {
+      const uint32_t li = (uint32_t)pc, q = (uint32_t)a.q;
+      const int lat[3] = {(int)(li % q), (int)((li / q) % q), (int)(li / (q * q))};
+      const int64_t pi = ((int64_t)((g.cz0 + o[2]) * a.q + lat[2]) * a.np + ((g.cy0 + o[1]) * a.q + lat[1])) * a.lat_pitch_f +
+                         ((g.cx0 + o[0]) * a.q + lat[0]);
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const float ps = (d == 0 ? a.psi0 : (d == 1 ? a.psi1 : a.psi2))[pi];
+        v[d] = a.vfac * ps;
+        l[d] = (float)(2 * lat[d] + 1) * a.lunit + ps;
+      }
+    } else {
+      const float4 cv = cellv[s];
+      const float vcv[3] = {cv.x, cv.y, cv.z};
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        int nuv = nuc[d];
+        nuv = nuv < -a.vhalf ? -a.vhalf : (nuv > a.vhalf ? a.vhalf : nuv);
+        l[d] = (float)(2 * ch[d] + 1) * unit;
+        v[d] = __builtin_fmaf(cv.w, tdec[nuv + a.vhalf], vcv[d]);
+      }
+    }
+    float vv = 0.f, tq = 0.f;
+    if constexpr (MODE == 0) {
+      // CIC corner relative to the tile, exact dyadic weights, interpolated gradient
+      int i0[3];
+      float w0[3], w1[3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const int pl = o[d] * (1 << (SH + 2)) + 2 * ch[d] + 1 - (1 << (SH - 1));
+        i0[d] = pl >> SH;
+        w1[d] = (float)(pl & ((1 << SH) - 1)) * unit;
+        w0[d] = 1.0f - w1[d];  // exact: both are multiples of 2^-SH in [0, 1]
+      }
+      const float* const corner = &ph[(i0[2] + 3) * CPP + (i0[1] + 3) * CPX + (i0[0] + 4)];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        constexpr int st[3] = {1, CPX, CPP};
+        const int e = st[d];
+        auto grad = [&](int x, int y, int z) {
+          const float* const f = corner + x + CPX * y + CPP * z;
+          const float aa = f[e] - f[-e], bb = f[2 * e] - f[-2 * e];
+          return __builtin_fmaf(8.0f, aa, -bb);  // 8 aa is exact: the same value as 8 aa - bb
+        };
+        float sacc[2];
+#pragma unroll
+        for (int cz = 0; cz < 2; ++cz) {
+          float racc[2];
+#pragma unroll
+          for (int cy = 0; cy < 2; ++cy) racc[cy] = __builtin_fmaf(w1[0], grad(1, cy, cz), w0[0] * grad(0, cy, cz));
+          sacc[cz] = __builtin_fmaf(w1[1], racc[1], w0[1] * racc[0]);
+        }
+        const float t = __builtin_fmaf(w1[2], sacc[1], w0[2] * sacc[0]);
+        v[d] = __builtin_fmaf(t, a.kf, v[d]);
+        if constexpr (MEAS) tq = d == 0 ? t * t : tq + t * t;
+      }
+      if constexpr (MEAS) vv = (v[0] * v[0] + v[1] * v[1]) + v[2] * v[2];
+    }
+    if constexpr (MEAS) {
+      vmax = fmaxf(vmax, active ? vv : 0.0f);
+      gmax = fmaxf(gmax, active ? tq : 0.0f);
+    }
+    if constexpr (MODE != 2) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) l[d] = __builtin_fmaf(v[d], a.df, l[d]);
+    }
+    // New cell and codes; the fast way when every particle of the chunk moves by at most one cell at a
+    // speed that both moment roundings take (NaN fails the comparisons)
+    int k[3], cq[3];
+    long long q[4];
+    bool usual = true;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) usual = usual & (l[d] >= -4.0f) & (l[d] < 8.0f) & (fabsf(v[d]) < 8192.0f);
+    if (__ballot(!usual) == 0ull) {
+      q[3] = 0;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const float kf = floorf(0.25f * l[d]);  // -1, 0 or 1
+        const int c = (int)floorf(__builtin_fmaf(-4.0f, kf, l[d]) * (float)(1 << (SH - 1)));
+        k[d] = (int)kf;
+        cq[d] = min(max(c, 0), (1 << (SH + 1)) - 1);
+        const double vd = (double)v[d];
+        q[d] = rint_ll(vd, 4294967296.0);
+        q[3] += rint_ll(vd * vd, 16777216.0);
+      }
+    } else {
+      bool ok = true;
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+        if (!new_cell<SH>(active ? l[d] : 0.0f, active ? v[d] : 0.0f, a.flags, k[d], cq[d])) ok = false;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) v[d] = ok ? v[d] : 0.0f;
+      velocity_moments(v, q);
+    }
+    const int dcode = 13 + k[0] + 3 * k[1] + 9 * k[2];
+    const bool stay = dcode == 13;
+    const int ring = 43 + o[0] + RG * o[1] + RG * RG * o[2] + k[0] + RG * k[1] + RG * RG * k[2];
+    const int slot = stay ? s * CCOPY + (lane & (CCOPY - 1)) : TC * CCOPY + ring;
+    if (active) {
+      if constexpr (MODE != 2)
+        if (a.rec) store_record<NCHI>(a, pc, v, cq, dcode);
+#pragma unroll
+      for (int d = 0; d < 4; ++d) atomicAdd(&mom[d * CSLOT + slot], (unsigned long long)q[d]);
+      if (!stay) atomicAdd(&left[s * 27 + dcode], 1u);
+    }
+  };
+  uint32_t c0 = 64u * (uint32_t)wave;
+  if (c0 < tot) {
+    locate(c0, sn, pn);
+    if constexpr (MODE != 2) wn.load(a.codes, a.cap, pn);
+  }
+  for (; c0 + 64u <= tot; c0 += 64u * NW) chunk(std::true_type{}, c0);
+  if (c0 < tot) chunk(std::false_type{}, c0);
+  if constexpr (MEAS) {
+    // one pair of device atomics per tile, and none once the maxima are higher
+    vmax = wave_max(vmax);
+    gmax = wave_max(gmax);
+    if (lane == 0) {
+      atomicMax(&top[0], __float_as_uint(vmax));
+      atomicMax(&top[1], __float_as_uint(gmax));
     }
   }
   __syncthreads();
-  flush_counts<NTH>(a, g, mcnt);
-  if constexpr (L::kGlobalMom) {
-    for (int i = threadIdx.x; i < TC * 4; i += NTH) {
-      const unsigned long long v = mom[i];
-      if (v == 0ull) continue;
-      const int so = i / 4, q = i % 4;
-      const int64_t c = (g.cx0 + so % T) + (int64_t)a.nc * ((g.cy0 + (so / T) % T) + (int64_t)a.nc * (g.cz0 + so / (T * T)));
-      atomicAdd(reinterpret_cast<unsigned long long*>(&a.mom[q * a.nc3 + c]), v);
+  if constexpr (MEAS) {
+    if (threadIdx.x < 2 && top[threadIdx.x] > __atomic_load_n(&a.amax[threadIdx.x], __ATOMIC_RELAXED))
+      atomicMax(&a.amax[threadIdx.x], top[threadIdx.x]);
+  }
+  // moments of the tile's and the ring's new cells, four to a cell
+  unsigned long long* const out = reinterpret_cast<unsigned long long*>(a.mom) + (uint64_t)lb * (4 * RC);
+  for (int i = threadIdx.x; i < 4 * RC; i += CNTH) {
+    const int d = i & 3, r = i >> 2;
+    const int rx = r % RG - 1, ry = (r / RG) % RG - 1, rz = r / (RG * RG) - 1;
+    unsigned long long v = mom[d * CSLOT + TC * CCOPY + r];
+    if ((unsigned)rx < (unsigned)T && (unsigned)ry < (unsigned)T && (unsigned)rz < (unsigned)T) {
+      const ulonglong2* const m = reinterpret_cast<const ulonglong2*>(&mom[d * CSLOT + (rx + T * (ry + T * rz)) * CCOPY]);
+#pragma unroll
+      for (int j = 0; j < CCOPY / 2; ++j) v += m[j].x + m[j].y;
     }
-  } else {
-    for (int i = threadIdx.x; i < RC * 4; i += NTH) {
-      const unsigned long long v = mom[i];
-      if (v == 0ull) continue;
-      const int r = i / 4, q = i % 4;
-      const int gx = wrapi(g.cx0 - 1 + r % RG, a.nc), gy = wrapi(g.cy0 - 1 + (r / RG) % RG, a.nc);
-      const int gz = wrapi(g.cz0 - 1 + r / (RG * RG), a.nc);
-      const int64_t c = gx + (int64_t)a.nc * (gy + (int64_t)a.nc * gz);
-      atomicAdd(reinterpret_cast<unsigned long long*>(&a.mom[q * a.nc3 + c]), v);
-    }
+    out[i] = v;
+  }
+  // counts: a wavefront writes one displacement of all own cells, a lane per cell; the wavefront that
+  // has displacement 13 takes the leavers from the cell's count
+  uint32_t* const col = a.mig + oc;
+  for (int d = wave; d < 27; d += NW) {
+    uint32_t n = d == 13 ? cnt : left[lane * 27 + d];
+    if (d == 13)
+      for (int j = 0; j < 27; ++j) n -= left[lane * 27 + j];  // entry 13 stays 0
+    (col + d * a.nc3)[0] = n;
   }
 }
 
-// at least six wavefronts per SIMD (three 512-thread workgroups per CU): at most 80 VGPRs
-template <int NCHI, int NNU, int MODE, bool PRE, int NTH, bool MEAS = false>
-__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(6))) void k_move_count(MoveArgs a) {
-  move_count_tile<NCHI, NNU, MODE, PRE, NTH, MEAS>(a, xcd_block(blockIdx.x, gridDim.x));
+template <int NCHI, int NNU, int MODE, bool MEAS = false>
+__global__ __launch_bounds__(CNTH) __attribute__((amdgpu_waves_per_eu(8))) void k_count(MoveArgs a) {
+  count_tile<NCHI, NNU, MODE, MEAS>(a, xcd_block(blockIdx.x, gridDim.x));
 }
 
 // every box of an ensemble in one launch (a box's workgroups: its tiles)
-template <int NCHI, int NNU, int MODE, bool PRE, int NTH>
-__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(6))) void k_move_count_boxes(BoxTable<MoveArgs> t) {
+template <int NCHI, int NNU>
+__global__ __launch_bounds__(CNTH) __attribute__((amdgpu_waves_per_eu(8))) void k_count_boxes(BoxTable<MoveArgs> t) {
   const unsigned l = xcd_block(blockIdx.x, gridDim.x);
   const int b = box_of(t.first, t.nbox, l);
-  move_count_tile<NCHI, NNU, MODE, PRE, NTH, false>(t.args[b], l - t.first[b]);
+  count_tile<NCHI, NNU, 0, false>(t.args[b], l - t.first[b]);
 }
 
 // Eq. (nu) by the edge table: the code nu with ext[nu + h] <= u < ext[nu + h + 1] (h = (M-1)/2;
@@ -1045,11 +1199,10 @@ __device__ __forceinline__ int encode_nu(float u, const float* ext, const BT* bu
   return nu;
 }
 
-template <int NCHI, int NNU, int MODE, bool PRE, int NTH>
+template <int NCHI, int NNU, int MODE, int NTH>
 __device__ __forceinline__ void move_scatter_tile(MoveArgs a, const unsigned lb) {
   resolve_factors(a);
-  __shared__ float ph[MoveLds<MODE, PRE>::kPh];
-  __shared__ float gd[MoveLds<MODE, PRE>::kGd];
+  __shared__ float ph[MODE == 0 ? PH * PH * PH : 1];
   __shared__ uint32_t grp[TC * 27];
   __shared__ uint32_t pre[TC + 1];
   __shared__ uint64_t start[TC];
@@ -1060,7 +1213,7 @@ __device__ __forceinline__ void move_scatter_tile(MoveArgs a, const unsigned lb)
   // returns then cannot hold up the others
   const uint32_t failed = __atomic_load_n(a.flags, __ATOMIC_RELAXED);
   const TileGeom g = tile_of(lb, a.nt);
-  load_potential<MODE, PRE, NTH>(a, ph, gd, g);
+  load_potential<MODE, NTH>(a, ph, g);
   for (int i = threadIdx.x; i < TC * 27; i += NTH) grp[i] = 0u;
   const int nedge = 2 * a.vhalf + 2;
   if constexpr (NNU == 1) {
@@ -1087,7 +1240,7 @@ __device__ __forceinline__ void move_scatter_tile(MoveArgs a, const unsigned lb)
       s = find_cell_in(pre, c0, c1, i);
       const uint32_t li = i - pre[s];
       const int64_t p = (int64_t)start[s] + li;
-      m = move_particle<NCHI, NNU, MODE, PRE>(a, ph, gd, s, p, li, g);
+      m = move_particle<NCHI, NNU, MODE>(a, ph, s, p, li, g);
       dcode = (m.k[2] + 1) * 9 + (m.k[1] + 1) * 3 + (m.k[0] + 1);
       key = s * 27 + dcode;
     }
@@ -1133,27 +1286,26 @@ __device__ __forceinline__ void move_scatter_tile(MoveArgs a, const unsigned lb)
   }
 }
 
-template <int NCHI, int NNU, int MODE, bool PRE, int NTH>
+template <int NCHI, int NNU, int MODE, int NTH>
 __global__ __launch_bounds__(NTH) void k_move_scatter(MoveArgs a) {
-  move_scatter_tile<NCHI, NNU, MODE, PRE, NTH>(a, xcd_block(blockIdx.x, gridDim.x));
+  move_scatter_tile<NCHI, NNU, MODE, NTH>(a, xcd_block(blockIdx.x, gridDim.x));
 }
 
-template <int NCHI, int NNU, int MODE, bool PRE, int NTH>
+template <int NCHI, int NNU, int MODE, int NTH>
 __global__ __launch_bounds__(NTH) void k_move_scatter_boxes(BoxTable<MoveArgs> t) {
   const unsigned l = xcd_block(blockIdx.x, gridDim.x);
   const int b = box_of(t.first, t.nbox, l);
-  move_scatter_tile<NCHI, NNU, MODE, PRE, NTH>(t.args[b], l - t.first[b]);
+  move_scatter_tile<NCHI, NNU, MODE, NTH>(t.args[b], l - t.first[b]);
 }
 
 // ---------------------------------------------------------------------------------------------
-// Dense move passes (at least half as many particles as fine cells): one coarse cell per wave at
-// a time, so the cell's offset, mean velocity and scale are wave-uniform; the stayers of a cell
-// (the large majority) are summed with one cross-lane reduction; particles of a cell are visited
-// in storage order by a single wave, which makes the running rank per displacement exact.
+// Recomputing scatter with the gradient tile (steps without records, where cells hold many particles):
+// the 4-point gradient of the whole tile is formed once in LDS, the tile's particles are shared by
+// all wavefronts in chunks of 64, and their ranks are taken in storage order.
 // ---------------------------------------------------------------------------------------------
 
-template <int NCHI, int NNU, bool SCATTER, bool MEAS>
-__device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
+template <int NCHI, int NNU>
+__device__ __forceinline__ void scatter_dense_tile(MoveArgs a, const unsigned lb) {
   resolve_factors(a);
   constexpr int NTH = 1024;
   constexpr int SH = 8 * NCHI - 1;
@@ -1164,16 +1316,16 @@ __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
   __shared__ float tile[NG];
   float* const ph = tile;
   float* const gd = tile;
-  __shared__ uint32_t grp[TC * 27];              // count pass: per (cell, displacement) counts; scatter: ranks
+  __shared__ uint32_t grp[TC * 27];              // particles ranked so far per (cell, displacement)
   __shared__ uint32_t pre[TC + 1];
   __shared__ uint64_t start[TC];
   __shared__ uint32_t wsum[NTH / 64];
   __shared__ float tdec_lds[NNU == 1 ? 255 : 1];
-  __shared__ float edges_lds[(SCATTER && NNU == 1) ? 256 : 1];
-  __shared__ int8_t bucket_lds[(SCATTER && NNU == 1) ? 1024 : 1];  // 1-byte codes fit int8
+  __shared__ float edges_lds[NNU == 1 ? 256 : 1];
+  __shared__ int8_t bucket_lds[NNU == 1 ? 1024 : 1];  // 1-byte codes fit int8
   const TileGeom g = tile_of(lb, a.nt);
-  // scatter: the flag word is requested first and tested after the set-up (the last barrier)
-  const uint32_t failed = SCATTER ? __atomic_load_n(a.flags, __ATOMIC_RELAXED) : 0u;
+  // the flag word is requested first and tested after the set-up (the last barrier)
+  const uint32_t failed = __atomic_load_n(a.flags, __ATOMIC_RELAXED);
   // mean velocity and decode scale of the tile's cells
   __shared__ float4 cellv[TC];
   uint32_t cnt_r = 0;  // particle count of own cell threadIdx.x
@@ -1185,10 +1337,8 @@ __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
     int bucket_r = 0;
     if constexpr (NNU == 1) {
       if (threadIdx.x < 255) tdec_r = a.tdec[threadIdx.x];
-      if constexpr (SCATTER) {
-        if (threadIdx.x < 256) edge_r = a.tedge[threadIdx.x];
-        if ((int)threadIdx.x < a.nbucket) bucket_r = a.tbucket[threadIdx.x];
-      }
+      if (threadIdx.x < 256) edge_r = a.tedge[threadIdx.x];
+      if ((int)threadIdx.x < a.nbucket) bucket_r = a.tbucket[threadIdx.x];
     }
     float4 cv_r = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     uint64_t start_r = 0;
@@ -1199,13 +1349,11 @@ __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
       start_r = a.off[c];
       cv_r = make_float4(a.vc[c], a.vc[a.nc3 + c], a.vc[2 * a.nc3 + c], a.vs[c]);
     }
-    load_potential<0, false, NTH>(a, ph, nullptr, g);
+    load_potential<0, NTH>(a, ph, g);
     if constexpr (NNU == 1) {
       if (threadIdx.x < 255) tdec_lds[threadIdx.x] = tdec_r;
-      if constexpr (SCATTER) {
-        if (threadIdx.x < 256) edges_lds[threadIdx.x] = edge_r;
-        if ((int)threadIdx.x < a.nbucket) bucket_lds[threadIdx.x] = (int8_t)bucket_r;
-      }
+      if (threadIdx.x < 256) edges_lds[threadIdx.x] = edge_r;
+      if ((int)threadIdx.x < a.nbucket) bucket_lds[threadIdx.x] = (int8_t)bucket_r;
     }
     if (threadIdx.x < TC) {
       cellv[threadIdx.x] = cv_r;
@@ -1248,7 +1396,7 @@ __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
     }
   }
   for (int i = threadIdx.x; i < TC * 27; i += NTH) grp[i] = 0u;
-  // scatter: [0] the number of the tile's chunks ranked so far, [1] set if a wait gave up
+  // [0] the number of the tile's chunks ranked so far, [1] set if a wait gave up
   __shared__ uint32_t turn[2];
   if (threadIdx.x == 0) turn[0] = turn[1] = 0u;
   const float* tdec = NNU == 1 ? tdec_lds : a.tdec;
@@ -1257,15 +1405,10 @@ __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
   const BT* bucket;
   if constexpr (NNU == 1) bucket = bucket_lds;
   else bucket = a.tbucket;
-  // count pass: moments of the new cells inside the tile, flushed to the global accumulators at the end
-  __shared__ unsigned long long omom[SCATTER ? 1 : TC * 4];
-  if constexpr (!SCATTER)
-    for (int i = threadIdx.x; i < TC * 4; i += NTH) omom[i] = 0ull;
   block_exclusive_scan(cnt_r, pre, TC, wsum);  // ends with a barrier
-  if (SCATTER && __builtin_amdgcn_readfirstlane(failed)) return;  // a failed step is not applied
+  if (__builtin_amdgcn_readfirstlane(failed)) return;  // a failed step is not applied
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const unsigned long long lt = (1ull << lane) - 1ull;
   const float unit = (float)(1.0 / (double)(1 << SH));
   // kick, drift, new cell and code of one particle (cell s at tile offsets (ci, o1, o2), codes chc,
   // nuc); inactive lanes keep v = l = 0
@@ -1273,7 +1416,6 @@ __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
                      int* cq) {
     float l[3] = {0.f, 0.f, 0.f};
     v[0] = v[1] = v[2] = 0.f;
-    float vv = 0.f, tq = 0.f;
     int ch[3] = {0, 0, 0};
     if (active) {
       const float4 cv = cellv[s];
@@ -1314,13 +1456,10 @@ __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
         }
         const float t = __builtin_fmaf(w1[2], sacc[1], w0[2] * sacc[0]);
         v[d] = __builtin_fmaf(t, a.kf, v[d]);
-        if constexpr (MEAS) tq = d == 0 ? t * t : tq + t * t;
       }
-      if constexpr (MEAS) vv = (v[0] * v[0] + v[1] * v[1]) + v[2] * v[2];
 #pragma unroll
       for (int d = 0; d < 3; ++d) l[d] = __builtin_fmaf(v[d], a.df, l[d]);
     }
-    if constexpr (MEAS) raise_maxima(a.amax, vv, tq);
     // new cell, codes, flags (same rules as the generic path)
     bool ok = true;
 #pragma unroll
@@ -1331,7 +1470,7 @@ __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
       for (int d = 0; d < 3; ++d) v[d] = 0.0f;
     }
   };
-  // Both passes: the wavefronts take every NW-th chunk of 64 of the tile's particles (its 64 cells
+  // The wavefronts take every NW-th chunk of 64 of the tile's particles (its 64 cells
   // in storage order, one after the other), so that a crowded cell is shared by all of them; the
   // lanes of a chunk find their cells from the prefix counts by a forward walk shared by the
   // wavefront.
@@ -1378,58 +1517,7 @@ __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
       int k[3], cq[3];
       physics(active, s, ci, o1, o2, chc, nuc, v, k, cq);
       const int dcode = (k[2] + 1) * 9 + (k[1] + 1) * 3 + (k[0] + 1);
-      if constexpr (!SCATTER) {
-        if (a.rec && active) store_record<NCHI>(a, pc, v, cq, dcode);
-        const uint32_t cbeg = pre[s], cend = pre[s + 1];
-        long long q[4];
-        velocity_moments(v, q);  // inactive lanes hold v = 0
-        const bool stay = active && dcode == 13;
-        const unsigned long long smask = __ballot(stay);
-        // stayers: one prefix sum over the chunk, then the difference over each cell's lanes
-        unsigned long long ps[4];
-#pragma unroll
-        for (int d = 0; d < 4; ++d) ps[d] = wave_scan_u64(stay ? (unsigned long long)q[d] : 0ull);
-        // The last lane of each of the chunk's cells adds the cell's stayers: their number
-        // and moment sums are the differences of the inclusive scans at that lane and at the lane
-        // before the cell's first one in the chunk (fetched with one lane shuffle per word).
-        const int la = cbeg > c0 ? (int)(cbeg - c0) : 0;  // the cell's first lane in the chunk
-        const int from = (la > 0 ? la - 1 : 0) * 4;
-        const bool tail = active && (i + 1u == cend || lane == 63);
-        const unsigned long long seg = (lane == 63 ? ~0ull : ((2ull << lane) - 1ull)) & ~((1ull << la) - 1ull);
-        const uint32_t nst = (uint32_t)__popcll(smask & seg);
-        unsigned long long sum4[4];
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)ps[d]);
-          const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(ps[d] >> 32));
-          sum4[d] = ps[d] - (la > 0 ? (((unsigned long long)hi << 32) | lo) : 0ull);
-        }
-        if (tail && nst > 0u) {
-          atomicAdd(&grp[s * 27 + 13], nst);
-#pragma unroll
-          for (int d = 0; d < 4; ++d) atomicAdd(&omom[s * 4 + d], sum4[d]);
-        }
-        if (active && !stay) {
-          atomicAdd(&grp[s * 27 + dcode], 1u);
-          // new cell inside the tile: the tile's LDS accumulators; in the ring: the global ones
-          const int tx = ci + k[0], ty = o1 + k[1], tz = o2 + k[2];
-          if (tx >= 0 && tx < T && ty >= 0 && ty < T && tz >= 0 && tz < T) {
-            const int so = tx + T * (ty + T * tz);
-#pragma unroll
-            for (int d = 0; d < 4; ++d) atomicAdd(&omom[so * 4 + d], (unsigned long long)q[d]);
-          } else {
-            // the cell index and byte offsets fit 32 bits (nc^3 < 2^28); the plane bases are uniform
-            const uint32_t nx = (uint32_t)wrapi(g.cx0 + tx, a.nc), ny = (uint32_t)wrapi(g.cy0 + ty, a.nc);
-            const uint32_t nz = (uint32_t)wrapi(g.cz0 + tz, a.nc), ncu = (uint32_t)a.nc;
-            const uint32_t boff = (nx + ncu * (ny + ncu * nz)) * 8u;
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-              char* plane = reinterpret_cast<char*>(a.mom + (int64_t)d * a.nc3);
-              atomicAdd(reinterpret_cast<unsigned long long*>(plane + boff), (unsigned long long)q[d]);
-            }
-          }
-        }
-      } else {
+      {
         // Scatter: the rank inside the (new cell, source offset) slot is the number of the
         // particles before this one in storage order with the same (source cell, displacement).
         // Within the chunk it comes from the lanes with the same key: the cell's lanes are one
@@ -1510,29 +1598,19 @@ __device__ __forceinline__ void move_dense_tile(MoveArgs a, const unsigned lb) {
       }
     }
   }
-  if constexpr (!SCATTER) {
-    __syncthreads();
-    flush_counts<NTH>(a, g, grp);
-    if (threadIdx.x < TC * 4) {
-      const int so = threadIdx.x / 4, d = threadIdx.x % 4;
-      const unsigned long long m = omom[threadIdx.x];
-      const int64_t c = (g.cx0 + so % T) + (int64_t)a.nc * ((g.cy0 + (so / T) % T) + (int64_t)a.nc * (g.cz0 + so / (T * T)));
-      if (m) atomicAdd(reinterpret_cast<unsigned long long*>(&a.mom[d * a.nc3 + c]), m);
-    }
-  }
 }
 
 // two 1024-thread workgroups per CU: at most 64 VGPRs
-template <int NCHI, int NNU, bool SCATTER, bool MEAS = false>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void k_move_dense(MoveArgs a) {
-  move_dense_tile<NCHI, NNU, SCATTER, MEAS>(a, xcd_block(blockIdx.x, gridDim.x));
+template <int NCHI, int NNU>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void k_scatter_dense(MoveArgs a) {
+  scatter_dense_tile<NCHI, NNU>(a, xcd_block(blockIdx.x, gridDim.x));
 }
 
-template <int NCHI, int NNU, bool SCATTER>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void k_move_dense_boxes(BoxTable<MoveArgs> t) {
+template <int NCHI, int NNU>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void k_scatter_dense_boxes(BoxTable<MoveArgs> t) {
   const unsigned l = xcd_block(blockIdx.x, gridDim.x);
   const int b = box_of(t.first, t.nbox, l);
-  move_dense_tile<NCHI, NNU, SCATTER, false>(t.args[b], l - t.first[b]);
+  scatter_dense_tile<NCHI, NNU>(t.args[b], l - t.first[b]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1732,7 +1810,7 @@ __global__ __launch_bounds__(PLACE_BLK) void k_place_boxes(BoxTable<MoveArgs> t)
 struct LinkArgs {
   uint32_t* mig;
   uint32_t* cnt_n;
-  int64_t* mom;
+  const int64_t* mom;  // the count pass's blocks per tile; load path: four planes of nc^3
   float* vc_n;
   double* dev;
   uint64_t* blk_n;
@@ -1749,8 +1827,7 @@ constexpr double kDevTermLimit = 18014398509481984.0;  // 2^54
 
 // Bound by memory latency, then by its 27 words read and written per cell: the 27 counts and the
 // four moments of a cell are requested together (with one load waiting for the store before it, a
-// 16^3 box took 15 us, 128^3 cells 139 us). Cell indices fit 32 bits (nc <= 512), plane
-// bases are uniform.
+// 16^3 box took 15 us). Cell indices fit 32 bits (nc <= 512), plane bases are uniform.
 __device__ __forceinline__ void link_block(const LinkArgs& a, const unsigned blk) {
   __shared__ unsigned long long sn[LINK_BLK / 64], sq[LINK_BLK / 64];
   if (workgroup_step_failed(a.flags)) return;
@@ -1758,13 +1835,44 @@ __device__ __forceinline__ void link_block(const LinkArgs& a, const unsigned blk
   uint32_t n = 0;
   long long q = 0;
   if (c < (uint32_t)a.nc3) {
-    unsigned long long* const mom = reinterpret_cast<unsigned long long*>(a.mom);
-    const long long s1x = (long long)mom[c], s1y = (long long)(mom + a.nc3)[c], s1z = (long long)(mom + 2 * a.nc3)[c],
-                    s2 = (long long)(mom + 3 * a.nc3)[c];
+    unsigned long long m4[4];
     if (a.cnt_direct) {
       n = a.cnt_direct[c];
+#pragma unroll
+      for (int d = 0; d < 4; ++d) m4[d] = (unsigned long long)(a.mom + d * a.nc3)[c];
     } else {
       const uint32_t x = c % nc, y = (c / nc) % nc, z = c / (nc * nc);
+      // the cell's entries in its own tile and in the tiles it lies in the ring of: beyond the lower or
+      // upper face along each axis on which the cell lies at its tile's face
+      const uint32_t nt = nc / T;
+      uint32_t tl[3][2], rl[3][2];  // per axis: own tile and ring coordinate, neighbour's
+      bool face[3];
+      const uint32_t xyz[3] = {x, y, z};
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const uint32_t t = xyz[d] / T, o = xyz[d] % T;
+        const bool lo = o == 0, hi = o == T - 1;
+        face[d] = lo || hi;
+        tl[d][0] = t;
+        rl[d][0] = o + 1;
+        tl[d][1] = lo ? (t ? t - 1 : nt - 1) : (t + 1 < nt ? t + 1 : 0);
+        rl[d][1] = lo ? T + 1 : 0;
+      }
+      m4[0] = m4[1] = m4[2] = m4[3] = 0;
+      const ulonglong2* const tab = reinterpret_cast<const ulonglong2*>(a.mom);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int ex = e & 1, ey = (e >> 1) & 1, ez = e >> 2;
+        if ((!ex || face[0]) && (!ey || face[1]) && (!ez || face[2])) {
+          const uint64_t t = tl[0][ex] + nt * (tl[1][ey] + (uint64_t)nt * tl[2][ez]);
+          const ulonglong2* const m = tab + (t * RC + rl[0][ex] + RG * (rl[1][ey] + RG * rl[2][ez])) * 2;
+          const ulonglong2 m01 = m[0], m23 = m[1];
+          m4[0] += m01.x;
+          m4[1] += m01.y;
+          m4[2] += m23.x;
+          m4[3] += m23.y;
+        }
+      }
       const uint32_t xs[3] = {x ? x - 1 : nc - 1, x, x + 1 < nc ? x + 1 : 0};
       const uint32_t ys[3] = {nc * (y ? y - 1 : nc - 1), nc * y, nc * (y + 1 < nc ? y + 1 : 0)};
       const uint32_t zs[3] = {nc * nc * (z ? z - 1 : nc - 1), nc * nc * z, nc * nc * (z + 1 < nc ? z + 1 : 0)};
@@ -1778,10 +1886,7 @@ __device__ __forceinline__ void link_block(const LinkArgs& a, const unsigned blk
       }
     }
     a.cnt_n[c] = n;
-    mom[c] = 0;
-    (mom + a.nc3)[c] = 0;
-    (mom + 2 * a.nc3)[c] = 0;
-    (mom + 3 * a.nc3)[c] = 0;
+    const long long s1x = (long long)m4[0], s1y = (long long)m4[1], s1z = (long long)m4[2], s2 = (long long)m4[3];
     double m0 = 0.0, m1 = 0.0, m2 = 0.0, dev = 0.0;
     const double nd = (double)n;
     if (n > 0) {
@@ -1827,11 +1932,12 @@ __device__ __forceinline__ void link_block(const LinkArgs& a, const unsigned blk
   }
 }
 
-__global__ __launch_bounds__(LINK_BLK) void k_link(LinkArgs a) { link_block(a, blockIdx.x); }
+__global__ __launch_bounds__(LINK_BLK) void k_link(LinkArgs a) { link_block(a, xcd_block(blockIdx.x, gridDim.x)); }
 
 __global__ __launch_bounds__(LINK_BLK) void k_link_boxes(BoxTable<LinkArgs> t) {
-  const int b = box_of(t.first, t.nbox, blockIdx.x);
-  link_block(t.args[b], blockIdx.x - t.first[b]);
+  const unsigned l = xcd_block(blockIdx.x, gridDim.x);
+  const int b = box_of(t.first, t.nbox, l);
+  link_block(t.args[b], l - t.first[b]);
 }
 
 // Nearest FP64 value (ties to even) of the unsigned 128-bit integer hi 2^64 + lo. Above 2^64 the
@@ -2284,14 +2390,11 @@ static MoveArgs move_args(const Sim& s, int cur, float kfac, float dfac, bool de
   return a;
 }
 
-// which kernel each move pass of a step (mode 0) uses: the gradient tile or the per-corner gradient
-static void move_kernels(const Sim& s, int mode, bool* tile_count, bool* tile_scatter) {
-  // gradient tile per pass: variant 1 both, 2 scatter only, 3 count only, -1 when particles are at
-  // least half as many as fine cells
+// whether a step's recomputing scatter uses the gradient tile: move_variant 1 and 2, -1 when there are
+// at least half as many particles as fine cells
+static bool tile_scatter(const Sim& s) {
   const bool dense = 2 * s.n >= (int64_t)s.nm * s.nm * s.nm;
-  const int mv = s.move_variant;
-  *tile_count = mode == 0 && (mv < 0 ? dense : (mv == 1 || mv == 3));
-  *tile_scatter = mode == 0 && (mv < 0 ? dense : (mv == 1 || mv == 2));
+  return s.move_variant < 0 ? dense : (s.move_variant == 1 || s.move_variant == 2);
 }
 
 void launch_move(Sim& s, int mode, float kfac, float dfac, float* const* psi, float vfac, hipStream_t st,
@@ -2316,25 +2419,21 @@ void launch_move(Sim& s, int mode, float kfac, float dfac, float* const* psi, fl
     a.lunit = (float)(2.0 / (double)a.q);
   }
   const unsigned grid = (unsigned)((int64_t)a.nt * a.nt * a.nt);
-  bool tile_count, tile_scatter;
-  move_kernels(s, mode, &tile_count, &tile_scatter);
 #define CUBE_COUNT(X, V)                                                                        \
   do {                                                                                          \
-    if (tile_count && a.amax) k_move_dense<X, V, false, true><<<grid, 1024, 0, st>>>(a);         \
-    else if (tile_count) k_move_dense<X, V, false><<<grid, 1024, 0, st>>>(a);                    \
-    else if (mode == 0 && a.amax) k_move_count<X, V, 0, false, 512, true><<<grid, 512, 0, st>>>(a); \
-    else if (mode == 0) k_move_count<X, V, 0, false, 512><<<grid, 512, 0, st>>>(a);              \
-    else if (mode == 1) k_move_count<X, V, 1, false, 256><<<grid, 256, 0, st>>>(a);              \
-    else k_move_count<X, V, 2, false, 256><<<grid, 256, 0, st>>>(a);                             \
+    if (mode == 0 && a.amax) k_count<X, V, 0, true><<<grid, CNTH, 0, st>>>(a);                   \
+    else if (mode == 0) k_count<X, V, 0><<<grid, CNTH, 0, st>>>(a);                              \
+    else if (mode == 1) k_count<X, V, 1><<<grid, CNTH, 0, st>>>(a);                              \
+    else k_count<X, V, 2><<<grid, CNTH, 0, st>>>(a);                                             \
   } while (0)
 #define CUBE_SCATTER(X, V)                                                                      \
   do {                                                                                          \
     if (mode != 2 && a.rec && a.pid_bytes) k_place<X, V, true><<<grid, PLACE_BLK, 0, st>>>(a);   \
     else if (mode != 2 && a.rec) k_place<X, V, false><<<grid, PLACE_BLK, 0, st>>>(a);            \
-    else if (tile_scatter) k_move_dense<X, V, true><<<grid, 1024, 0, st>>>(a);                   \
-    else if (mode == 0) k_move_scatter<X, V, 0, false, 512><<<grid, 512, 0, st>>>(a);            \
-    else if (mode == 1) k_move_scatter<X, V, 1, false, 256><<<grid, 256, 0, st>>>(a);            \
-    else k_move_scatter<X, V, 2, false, 256><<<grid, 256, 0, st>>>(a);                           \
+    else if (mode == 0 && tile_scatter(s)) k_scatter_dense<X, V><<<grid, 1024, 0, st>>>(a);                   \
+    else if (mode == 0) k_move_scatter<X, V, 0, 512><<<grid, 512, 0, st>>>(a);            \
+    else if (mode == 1) k_move_scatter<X, V, 1, 256><<<grid, 256, 0, st>>>(a);            \
+    else k_move_scatter<X, V, 2, 256><<<grid, 256, 0, st>>>(a);                           \
   } while (0)
   if (evs) CUBE_HIP(hipEventRecord(evs[0], st));
   CUBE_XV_DISPATCH(s.nchi, s.nnu, CUBE_COUNT);
@@ -2450,9 +2549,7 @@ void ensemble_move(EnsembleStep& es, const std::vector<Sim*>& boxes) {
         std::vector<MoveArgs> args;
         std::vector<uint32_t> per;
         for (Sim* s : boxes) {
-          bool tc, ts;
-          move_kernels(*s, 0, &tc, &ts);
-          const int kern = scatter ? (use_records(*s) ? (s->pid_bytes ? 3 : 2) : (ts ? 1 : 0)) : (tc ? 1 : 0);
+          const int kern = scatter ? (use_records(*s) ? (s->pid_bytes ? 3 : 2) : (tile_scatter(*s) ? 1 : 0)) : 0;
           if (s->nchi != nchi || s->nnu != nnu || kern != tile) continue;
           args.push_back(move_args(*s, s->cur, 0.0f, 0.0f, true));
           const int64_t nt = s->nc / T;
@@ -2466,10 +2563,9 @@ void ensemble_move(EnsembleStep& es, const std::vector<Sim*>& boxes) {
   do {                                                                                                  \
     if (tile == 3) k_place_boxes<X, V, true><<<g.blocks, PLACE_BLK, 0, st>>>(t);                         \
     else if (tile == 2) k_place_boxes<X, V, false><<<g.blocks, PLACE_BLK, 0, st>>>(t);                   \
-    else if (tile && scatter) k_move_dense_boxes<X, V, true><<<g.blocks, 1024, 0, st>>>(t);                   \
-    else if (tile) k_move_dense_boxes<X, V, false><<<g.blocks, 1024, 0, st>>>(t);                        \
-    else if (scatter) k_move_scatter_boxes<X, V, 0, false, 512><<<g.blocks, 512, 0, st>>>(t);            \
-    else k_move_count_boxes<X, V, 0, false, 512><<<g.blocks, 512, 0, st>>>(t);                           \
+    else if (tile && scatter) k_scatter_dense_boxes<X, V><<<g.blocks, 1024, 0, st>>>(t);                   \
+    else if (scatter) k_move_scatter_boxes<X, V, 0, 512><<<g.blocks, 512, 0, st>>>(t);            \
+    else k_count_boxes<X, V><<<g.blocks, CNTH, 0, st>>>(t);                                              \
   } while (0)
           CUBE_XV_DISPATCH(nchi, nnu, CUBE_PASS);
 #undef CUBE_PASS
@@ -2527,6 +2623,7 @@ void launch_load(Sim& s, const double* dx, const float* /*unused*/, int64_t n, h
   uint16_t* chi_tmp = static_cast<uint16_t*>(s.dmalloc(sizeof(uint16_t) * 3 * n));
   float* v_tmp = static_cast<float*>(s.dmalloc(sizeof(float) * 3 * n));
   CUBE_HIP(hipMemsetAsync(s.cnt[nxt], 0, sizeof(uint32_t) * s.nc3, st));
+  CUBE_HIP(hipMemsetAsync(s.mom, 0, sizeof(int64_t) * 4 * s.nc3, st));
   LoadArgs a;
   a.x = dx;
   a.v = dx + 3 * n;
