@@ -320,9 +320,8 @@ typedef struct {
                               nm_side <= 512, 4 or 8 above */
   int32_t fft_z_order;     /* workgroup order of the z passes: 0 dispatch order, 1 contiguous ranges
                               per XCD */
-  int32_t deposit_variant; /* bit 0: particles of a layer visited with a stride of 1/64 of the layer
-                              (lanes of a wavefront in different cells); bit 1: 512-thread
-                              workgroups instead of 256; default 3 */
+  int32_t deposit_variant; /* 0 .. 3 (default 3), without effect: the deposit has one kernel per
+                              mesh size and position code */
   int32_t fft_z_layout;    /* 0 (default): z pass in place on the mesh; 1: the forward y pass writes
                               a z-contiguous copy, the z pass works there and the inverse y pass
                               writes back (one more mesh-sized device buffer, allocated when chosen

@@ -1041,8 +1041,14 @@ int cube_set_state(cube_sim* sim, const cube_state_view* in) {
     CUBE_HIP(hipMemcpyAsync(s.off[c], off.data(), sizeof(uint64_t) * (s.nc3 + 1), hipMemcpyHostToDevice, st));
     void *chi, *nu;
     cube::staged_planes(s, &chi, &nu);
-    CUBE_HIP(hipMemcpyAsync(chi, in->chi, (size_t)3 * s.n * s.nchi, hipMemcpyHostToDevice, st));
-    CUBE_HIP(hipMemcpyAsync(nu, in->nu, (size_t)3 * s.n * s.nnu, hipMemcpyHostToDevice, st));
+    for (int d = 0; d < 3; ++d) {
+      CUBE_HIP(hipMemcpyAsync(static_cast<char*>(chi) + (size_t)d * s.n * s.nchi,
+                              static_cast<const char*>(in->chi) + (size_t)d * s.n * s.nchi, (size_t)s.n * s.nchi,
+                              hipMemcpyHostToDevice, st));
+      CUBE_HIP(hipMemcpyAsync(static_cast<char*>(nu) + (size_t)d * s.n * s.nnu,
+                              static_cast<const char*>(in->nu) + (size_t)d * s.n * s.nnu, (size_t)s.n * s.nnu,
+                              hipMemcpyHostToDevice, st));
+    }
     cube::launch_pack_codes(s, st);
     CUBE_HIP(hipMemcpyAsync(s.vc[c], in->vc, sizeof(float) * 3 * s.nc3, hipMemcpyHostToDevice, st));
     CUBE_HIP(hipMemcpyAsync(s.vs[c], in->vs, sizeof(float) * s.nc3, hipMemcpyHostToDevice, st));

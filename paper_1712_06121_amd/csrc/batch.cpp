@@ -165,7 +165,7 @@ float elapsed_ms(hipEvent_t a, hipEvent_t z) {
   return ms;
 }
 
-// Time the equivalent variants of the deposit, of the FFT column passes and of the move passes on
+// Time the deposit and the equivalent variants of the FFT column passes and of the scatter on
 // the current state and keep the fastest of each. The particle state is left unchanged (timed
 // moves write only the next-state buffers and scratch, and the parity is restored); the mesh is
 // left holding the potential of the current state.
@@ -184,29 +184,17 @@ void autotune_sim(Sim& s) {
     }
     return t;
   };
-  // deposit: particle order and workgroup size
   std::string rep;
   auto note = [&](const std::string& what, float ms) {
     char b[96];
     std::snprintf(b, sizeof(b), "%s %.3f ms; ", what.c_str(), ms / reps);
     rep += b;
   };
-  int best_d = s.deposit_variant;
-  float best = 1e30f;
-  for (int v : {0, 1, 2, 3}) {
-    s.deposit_variant = v;
-    const float t = timed([&] { launch_deposit(s, s.stream); });
-    note("deposit " + std::to_string(v), t);
-    if (t < best) {
-      best = t;
-      best_d = v;
-    }
-  }
-  s.deposit_variant = best_d;
+  note("deposit", timed([&] { launch_deposit(s, s.stream); }));
   // FFT column width, z-pass workgroup order and z layout (the scratch layout only if its buffer
   // can be allocated)
   int best_bx = s.mesh_plan.colbx, best_z = s.mesh_plan.zorder, best_l = s.mesh_plan.zlayout;
-  best = 1e30f;
+  float best = 1e30f;
   const bool had_scratch = s.mesh_plan.zscratch != nullptr;
   try {
     set_z_layout(s, 1);

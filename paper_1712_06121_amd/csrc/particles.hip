@@ -254,15 +254,18 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
   return t;
 }
 
-__device__ __forceinline__ int find_cell(const uint32_t* pre, int ncell, uint32_t i) {
-  int lo = 0, hi = ncell;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (pre[mid] <= i) lo = mid;
-    else hi = mid;
-  }
-  return lo;
+// sum over the 64 lanes (every lane active), in all lanes
+__device__ __forceinline__ uint32_t wave_total(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
+  v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+  v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, true);  // row_half_mirror
+  v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, true);  // row_mirror: the 16-lane row's sum
+  uint32_t t = 0;
+#pragma unroll
+  for (int r = 15; r < 64; r += 16) t += (uint32_t)__builtin_amdgcn_readlane((int)v, r);
+  return t;
 }
+__device__ __forceinline__ unsigned long long wave_total(unsigned long long v) { return wave_sum_u64(v); }
 
 struct TileGeom {
   int cx0, cy0, cz0;
@@ -285,161 +288,240 @@ struct DepArgs {
   int64_t cap;
   float* mesh;
   int64_t pitch_f;
-  int nm, nc, nt;
+  int nm, nc;
   int zc;  // coarse layers per z chunk
   double inv_mean;
-  int interleave;  // visit a layer's particles with a stride (fewer lanes adding to one cell at once)
 };
 
-constexpr int DTX = 8;            // coarse cells per column side
-constexpr int DF = 4 * DTX;       // fine cells per column side
-constexpr int DR = DTX + 2;       // source cells per side (column + ring)
-constexpr int DRC = DR * DR;      // source cells per coarse layer
-constexpr int NSLOT = 6;          // fine planes a coarse layer can touch
+constexpr int NSLOT = 6;  // fine planes a coarse layer can touch
+constexpr int MANY = 12;  // lanes on one corner cell from which their weights are summed before the LDS add
 
-__device__ __forceinline__ int slot_of(int p) { return ((p % NSLOT) + NSLOT) % NSLOT; }
+// Streaming gather: the workgroup owns a column of DTX x DTX coarse cells (DF = 4 DTX fine cells a
+// side) over the fine planes of coarse layers [cz0, cz1). It walks the source coarse layers
+// cz0-1 .. cz1 in order, each time reading the particles of the DR x DR cells (column + ring), and adds
+// exact integer CIC weights to a rolling set of NSLOT fine planes in LDS. After layer sz, planes up
+// to 4 sz + 2 receive no more mass: those it owns are converted once to FP32 delta and written, and
+// all their slots cleared.
+//
+// The planes in LDS have a border of one cell, so that the eight corners of a particle that reaches the
+// column are added without a test: border cells and planes outside [4 cz0, 4 cz1) collect what nobody
+// reads. A particle of the ring that reaches nothing is skipped by one comparison of its corner.
+//
+// Bound by vector issue where particles are spread (116 instructions per 64 particles of the column) and by
+// LDS adds to one address where they cluster. With 512^3 particles on as many cells 1075 -> 749 us early
+// and 1370 -> 993 clustered against columns with a tested corner each and 4 layers a chunk; 256^3 on
+// 512^3 cells 412 -> 370.
+template <int DTX>
+struct DepCfg {
+  static constexpr int DF = 4 * DTX;
+  static constexpr int DR = DTX + 2, DRC = DR * DR;
+  static constexpr int PX = DF + 3, PLANE = PX * (DF + 2);  // bordered plane (an odd pitch spreads the banks)
+};
 
-// Streaming gather: the workgroup owns a DF x DF column of fine cells over the fine planes of
-// coarse layers [cz0, cz1). It walks the source coarse layers cz0-1 .. cz1 in order, each time
-// reading the particles of the DR x DR cells (column + ring), and adds exact integer CIC weights
-// to a rolling set of NSLOT fine planes in LDS. After layer sz, planes up to 4 sz + 2 receive no
-// more mass: they are converted once to FP32 delta, written, and their slots reused.
-template <int NCHI, int BLK>
+template <int NCHI, int DTX, int BLK>
 __device__ __forceinline__ void deposit_column(const DepArgs& a, const unsigned lb) {
   constexpr int SH = 8 * NCHI - 1;
-  __shared__ unsigned long long rho[NSLOT * DF * DF];
-  __shared__ uint32_t pre[DRC + 1];
-  __shared__ uint64_t start[DRC];
-  __shared__ uint32_t wsum[BLK / 64];
-  // owner[k]: the source cell holding layer particle k << osh (a sparse index into pre, so that a
-  // particle's cell is found by a short forward scan instead of a binary search)
-  constexpr int NOWN = 1024;
-  static_assert(DRC < 256, "cell indices fit a byte");
-  __shared__ uint8_t owner[NOWN];
-  const unsigned cols = (unsigned)(a.nt * a.nt);
+  using C = DepCfg<DTX>;
+  constexpr int DF = C::DF, DR = C::DR, DRC = C::DRC, PX = C::PX, PLANE = C::PLANE;
+  static_assert(DRC <= 128, "source cells in two lane registers");
+  __shared__ __align__(16) unsigned long long rho[NSLOT * PLANE];
+  __shared__ uint32_t cbeg[(DRC > 64 ? DRC : 64) + 1];
+  __shared__ uint64_t crel[DRC > 64 ? DRC : 64];
+  __shared__ int corner[DRC];  // word of fine cell (0, 0) of a source cell in a bordered plane
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const unsigned ncol = (unsigned)(a.nc / DTX), cols = ncol * ncol;
   const unsigned bxy = lb % cols, bz = lb / cols;
-  const int cx0 = (bxy % a.nt) * DTX, cy0 = (bxy / a.nt) * DTX;
-  const int cz0 = bz * a.zc;
+  const int cx0 = (int)(bxy % ncol) * DTX, cy0 = (int)(bxy / ncol) * DTX;
+  const int cz0 = (int)bz * a.zc;
   const int cz1 = min(cz0 + a.zc, a.nc);
   const int pz0 = 4 * cz0, pz1 = 4 * cz1;  // owned fine planes [pz0, pz1)
-  for (int i = threadIdx.x; i < NSLOT * DF * DF; i += BLK) rho[i] = 0ull;
-  // 32-bit accumulators: a fine cell receives mass only from particles of the (at most 8) coarse
-  // cells around it, each weighing 2^(3 SH) in total; with 1-byte codes and at most 255 particles
-  // in every source cell of this workgroup the sum stays below 8 * 255 * 2^21 < 2^32
+  for (int i = threadIdx.x; i < NSLOT * PLANE / 2; i += BLK) reinterpret_cast<uint4*>(rho)[i] = make_uint4(0u, 0u, 0u, 0u);
+  if (threadIdx.x < DRC) corner[threadIdx.x] = ((int)threadIdx.x / DR * 4 - 3) * PX + ((int)threadIdx.x % DR * 4 - 3);
+  // 32-bit accumulators where no sum can reach 2^32: a fine cell receives mass only from particles of
+  // the 2^3 coarse cells around it, each weighing 2^(3 SH) in total, so with 1-byte codes 2047 particles
+  // in every such block of the workgroup's source cells are few enough
   __shared__ uint32_t smax;
   if (threadIdx.x == 0) smax = 0u;
   __syncthreads();
   if constexpr (NCHI == 1) {
+    const int nb = (DR - 1) * (DR - 1) * (cz1 - cz0 + 1);
     uint32_t m = 0u;
-    const int ncell = DRC * (cz1 - cz0 + 2);
-    for (int i = threadIdx.x; i < ncell; i += BLK) {
-      const int t = i % DRC, sz = cz0 - 1 + i / DRC;
-      const int sx = t % DR - 1, sy = t / DR - 1;
-      const uint32_t c = a.cnt[wrapi(cx0 + sx, a.nc) + (int64_t)a.nc * (wrapi(cy0 + sy, a.nc) + (int64_t)a.nc * wrapi(sz, a.nc))];
-      m = c > m ? c : m;
+    for (int i = threadIdx.x; i < nb; i += BLK) {
+      const int bx = i % (DR - 1), by = (i / (DR - 1)) % (DR - 1), bzz = i / ((DR - 1) * (DR - 1));
+      uint32_t n = 0u;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const uint32_t c = (uint32_t)wrapi(cx0 - 1 + bx + (j & 1), a.nc) +
+                           (uint32_t)a.nc * ((uint32_t)wrapi(cy0 - 1 + by + ((j >> 1) & 1), a.nc) +
+                                             (uint32_t)a.nc * (uint32_t)wrapi(cz0 - 1 + bzz + (j >> 2), a.nc));
+        n += min(a.cnt[c], 4096u);
+      }
+      m = max(m, n);
     }
-    atomicMax(&smax, m);
+    if (m > 2047u) atomicMax(&smax, m);
   }
   __syncthreads();
-  const bool narrow = NCHI == 1 && smax <= 255u;
-  uint32_t* rho32 = reinterpret_cast<uint32_t*>(rho);
-  for (int sz = cz0 - 1; sz <= cz1; ++sz) {
-    uint32_t cntv = 0;
-    if (threadIdx.x < DRC) {
-      const int sx = threadIdx.x % DR - 1, sy = threadIdx.x / DR - 1;
-      const int64_t c = wrapi(cx0 + sx, a.nc) + (int64_t)a.nc * (wrapi(cy0 + sy, a.nc) + (int64_t)a.nc * wrapi(sz, a.nc));
-      cntv = a.cnt[c];
-      start[threadIdx.x] = a.off[c];
+  const bool narrow = NCHI == 1 && smax <= 2047u;
+  // the layer's source cells in the lanes of every wavefront: cells 0 .. 63 and 64 .. DRC - 1
+  uint32_t inc[2], tot;
+  uint64_t rel[2];
+  uint32_t cnt_n[2];
+  uint64_t off_n[2];
+  auto request = [&](int sz) {
+    const int gz = wrapi(sz, a.nc);
+#pragma unroll
+    for (int h = 0; h < (DRC > 64 ? 2 : 1); ++h) {
+      const int t = lane + 64 * h;
+      cnt_n[h] = 0u;
+      off_n[h] = 0u;
+      if (t < DRC) {
+        const uint32_t c = (uint32_t)wrapi(cx0 + t % DR - 1, a.nc) +
+                           (uint32_t)a.nc * ((uint32_t)wrapi(cy0 + t / DR - 1, a.nc) + (uint32_t)a.nc * (uint32_t)gz);
+        cnt_n[h] = a.cnt[c];
+        off_n[h] = a.off[c];
+      }
     }
-    const uint32_t total = block_exclusive_scan(cntv, pre, DRC, wsum);
-    const uint32_t q64 = total / 64;
-    int osh = 4;
-    while ((total >> osh) >= (uint32_t)NOWN) ++osh;
-    if (threadIdx.x < DRC) {
-      const uint32_t lo = pre[threadIdx.x], hi = pre[threadIdx.x + 1];
-      for (uint32_t k = (lo + (1u << osh) - 1) >> osh; (k << osh) < hi; ++k) owner[k] = (uint8_t)threadIdx.x;
+  };
+  request(cz0 - 1);
+  uint32_t* const rho32 = reinterpret_cast<uint32_t*>(rho);
+  int first = ((4 * (cz0 - 1) - 1) % NSLOT + NSLOT) % NSLOT;  // slot of plane 4 sz - 1
+  for (int sz = cz0 - 1; sz <= cz1; ++sz, first = first + 4 >= NSLOT ? first + 4 - NSLOT : first + 4) {
+    inc[0] = (uint32_t)wave_scan_u64(cnt_n[0]);
+    rel[0] = off_n[0] - (inc[0] - cnt_n[0]);
+    tot = (uint32_t)__builtin_amdgcn_readlane((int)inc[0], 63);
+    if constexpr (DRC > 64) {
+      inc[1] = tot + (uint32_t)wave_scan_u64(cnt_n[1]);
+      rel[1] = off_n[1] - (inc[1] - cnt_n[1]);
+      tot = (uint32_t)__builtin_amdgcn_readlane((int)inc[1], 63);
+    }
+    if (wave == 0) {
+      cbeg[lane] = inc[0] - cnt_n[0];
+      crel[lane] = rel[0];
+      if (DRC > 64 && lane + 64 < DRC) {
+        cbeg[lane + 64] = inc[1] - cnt_n[1];
+        crel[lane + 64] = rel[1];
+      }
+      if (lane == 0) cbeg[DRC] = tot;
     }
     __syncthreads();
-    auto deposit_layer = [&](auto* acc) {
-    using A = typename std::remove_pointer<decltype(acc)>::type;
-    // source cell and codes of the layer's it-th particle
-    using Word = Codes<NCHI, 1>;  // its first plane is the same for every velocity code
-    auto fetch = [&](uint32_t it, int& s, Word& w) {
-      // interleaved: lane l of the w-th group of 64 takes particle l * (total / 64) + w, so the lanes
-      // of one wavefront hold particles of different cells (a bijection on [0, 64 * (total / 64)))
-      const uint32_t i = (a.interleave && it < 64 * q64) ? (it % 64) * q64 + it / 64 : it;
-      s = owner[i >> osh];
-      while (pre[s + 1] <= i) ++s;
-      w.load_chi(a.codes, (int64_t)start[s] + (i - pre[s]));
-    };
-    // CIC of one particle with source cell s and codes ch
-    auto deposit_one = [&](const int s, const Word& w) {
-      int ch[3];
-      w.chi(ch);
-      // the three codes are needed here on every path: without this the compiler may move their
-      // uses into the conditional corners and then wait conservatively for later loads as well
-      asm volatile("" ::"v"(ch[0]), "v"(ch[1]), "v"(ch[2]));
-      const int sl[3] = {s % DR - 1, s / DR - 1, sz};
-      int i0[3], w1[3];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        const int pl = sl[d] * (1 << (SH + 2)) + 2 * ch[d] + 1 - (1 << (SH - 1));
-        i0[d] = pl >> SH;
-        w1[d] = pl & ((1 << SH) - 1);
+    // lanes share a cell where it holds a good part of the layer's particles
+    bool crowded = __ballot((uint64_t)cnt_n[0] * 64u >= (uint64_t)MANY * tot) != 0ull;
+    if constexpr (DRC > 64) crowded |= __ballot((uint64_t)cnt_n[1] * 64u >= (uint64_t)MANY * tot) != 0ull;
+    if (sz < cz1) request(sz + 1);
+    const int zmin = pz0 - 1 - 4 * sz, zmax = pz1 - 1 - 4 * sz;  // corner planes that reach the owned ones
+    auto deposit_layer = [&](auto* acc, auto crowd) {
+      using A = typename std::remove_pointer<decltype(acc)>::type;
+      using W = std::conditional_t<NCHI == 1, uint32_t, unsigned long long>;  // weights, and their sum over 64 lanes
+      using Word = Codes<NCHI, 1>;  // its first plane is the same for every velocity code
+      // lane l takes the particles l len + wave, l len + wave + NW, ... of the layer: the lanes of a
+      // wavefront add to different parts of the column (64 neighbours in storage order take 1907 us with
+      // 512^3 clustered particles, runs of 16 and 4 lanes 1681 and 1251, this 993), and each lane's cell
+      // follows by a cursor that moves forward only
+      constexpr uint32_t NW = BLK / 64;
+      const uint32_t len = (tot + 63u) / 64u, b0 = (uint32_t)lane * len, e0 = min(b0 + len, tot);
+      int cur = 0;
+      uint32_t cend = 0;
+      {
+        const uint32_t i = min(b0 + (uint32_t)wave, tot - 1u);
+        int hi = DRC;
+        while (hi - cur > 1) {
+          const int mid = (cur + hi) >> 1;
+          if (cbeg[mid] <= i) cur = mid;
+          else hi = mid;
+        }
+        cend = cbeg[cur + 1];
       }
-      // weight products: < 2^(3 SH) -- 32-bit arithmetic for 1-byte codes, one 64-bit product else
-      const uint32_t wz2[2] = {(uint32_t)((1 << SH) - w1[2]), (uint32_t)w1[2]};
-      const uint32_t wy2[2] = {(uint32_t)((1 << SH) - w1[1]), (uint32_t)w1[1]};
-      const uint32_t wx2[2] = {(uint32_t)((1 << SH) - w1[0]), (uint32_t)w1[0]};
+      // source cell and position word of this lane's particle o (past its last one: some particle)
+      auto fetch = [&](uint32_t o, int& sc, Word& w) {
+        const uint32_t i = min(b0 + o, tot - 1u);
+        while (cend <= i) cend = cbeg[++cur + 1];
+        sc = cur;
+        w.load_chi(a.codes, (int64_t)(crel[cur] + i));
+      };
+      auto deposit_one = [&](const bool active, const int s, const Word& w) {
+        int ch[3];
+        w.chi(ch);
+        // corner relative to the source cell (-1 .. 3) and weight numerators
+        int i0[3];
+        uint32_t w1[3];
 #pragma unroll
-      for (int dz = 0; dz < 2; ++dz) {
-        const int pz = i0[2] + dz;
-        if (pz < pz0 || pz >= pz1) continue;
-        const int sb = slot_of(pz) * DF * DF;
+        for (int d = 0; d < 3; ++d) {
+          const int pl = 2 * ch[d] + 1 - (1 << (SH - 1));
+          i0[d] = pl >> SH;
+          w1[d] = (uint32_t)pl & ((1u << SH) - 1u);
+        }
+        const int sx = s % DR, sy = s / DR;
+        const int gx = 4 * sx + i0[0] - 3, gy = 4 * sy + i0[1] - 3;  // 0 .. DF: reaches the column
+        const bool reach = active && (unsigned)gx <= (unsigned)DF && (unsigned)gy <= (unsigned)DF && i0[2] >= zmin && i0[2] <= zmax;
+        int sl = first + 1 + i0[2];
+        sl = sl >= NSLOT ? sl - NSLOT : sl;
+        const int at = corner[s] + i0[1] * PX + i0[0];  // the corner's word in a bordered plane
+        const int up = sl + 1 >= NSLOT ? 0 : sl + 1;
+        const uint32_t one = 1u << SH;
+        const uint32_t wy2[2] = {one - w1[1], w1[1]}, wx2[2] = {one - w1[0], w1[0]}, wz2[2] = {one - w1[2], w1[2]};
+        // weight products: < 2^(3 SH) -- 24-bit factors for 1-byte codes, one 64-bit product else
+        auto weight = [&](int j) {
+          const uint32_t wzy = NCHI == 1 ? __umul24(wz2[j >> 2], wy2[(j >> 1) & 1]) : wz2[j >> 2] * wy2[(j >> 1) & 1];
+          return NCHI == 1 ? (W)__umul24(wzy, wx2[j & 1]) : (W)((unsigned long long)wzy * (unsigned long long)wx2[j & 1]);
+        };
+        auto word = [&](int j) { return ((j >> 2) ? up : sl) * PLANE + at + ((j >> 1) & 1) * PX + (j & 1); };
+        // An LDS add takes 2 cycles per lane on one address. Where MANY lanes or more share a corner cell (the
+        // core of a halo: all 64 in the worst case, 1000 cycles for the eight adds) their weights are
+        // summed over the wavefront first
+        unsigned long long todo = __ballot(reach);
+        const int key = sl * PLANE + at;
+        while (decltype(crowd)::value && todo) {
+          const int lead = __builtin_amdgcn_readlane(key, __ffsll((long long)todo) - 1);
+          const unsigned long long same = __ballot(key == lead) & todo;
+          if (__popcll(same) < MANY) break;
+          const bool in = (same >> lane) & 1ull;
 #pragma unroll
-        for (int dy = 0; dy < 2; ++dy) {
-          const int y = i0[1] + dy;
-          if (y < 0 || y >= DF) continue;
-          const uint32_t wzy = wz2[dz] * wy2[dy];
-#pragma unroll
-          for (int dx = 0; dx < 2; ++dx) {
-            const int x = i0[0] + dx;
-            if (x < 0 || x >= DF) continue;
-            const A m = NCHI == 1 ? (A)(wzy * wx2[dx]) : (A)((unsigned long long)wzy * (unsigned long long)wx2[dx]);
-            atomicAdd(&acc[sb + y * DF + x], m);
+          for (int j = 0; j < 8; ++j) {
+            const W t = wave_total(in ? weight(j) : (W)0);
+            if (lane == 63 - j) atomicAdd(acc + __builtin_amdgcn_readlane(word(j), __ffsll((long long)same) - 1), (A)t);
           }
+          todo &= ~same;
+        }
+        if (decltype(crowd)::value ? (todo >> lane) & 1ull : reach) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) atomicAdd(acc + word(j), (A)weight(j));
+        }
+      };
+      // software pipeline, unrolled twice so that the two particles' registers alternate: a wavefront
+      // requests the codes of its next chunk before it adds the current one
+      uint32_t o = (uint32_t)wave;
+      if (o < len) {
+        int s0, s1;
+        Word w0, w1;
+        fetch(o, s0, w0);
+        while (true) {
+          const uint32_t o1 = o + NW;
+          if (o1 < len) fetch(o1, s1, w1);
+          deposit_one(b0 + o < e0, s0, w0);
+          if (o1 >= len) break;
+          o = o1 + NW;
+          if (o < len) fetch(o, s0, w0);
+          deposit_one(b0 + o1 < e0, s1, w1);
+          if (o >= len) break;
         }
       }
     };
-    // software pipeline, unrolled twice so that the two particles' registers alternate: a thread
-    // requests the codes of its next particle before it computes the weights and issues the LDS
-    // atomics of the current one, so the global-memory latency overlaps them. The requests are
-    // unconditional (past the end they repeat the layer's last particle, whose codes go unused) so
-    // that the wait for the current codes never waits for the next ones.
-    if (total > 0) {
-      const uint32_t last = total - 1;
-      int s0, s1;
-      Word ch0, ch1;
-      fetch(min((uint32_t)threadIdx.x, last), s0, ch0);
-      for (uint32_t it = threadIdx.x; it < total; it += 2 * BLK) {
-        fetch(min(it + BLK, last), s1, ch1);
-        deposit_one(s0, ch0);
-        if (it + BLK >= total) break;
-        fetch(min(it + 2 * BLK, last), s0, ch0);
-        deposit_one(s1, ch1);
-      }
+    if (tot > 0u) {
+      if (narrow && !crowded) deposit_layer(rho32, std::false_type{});
+      else if (narrow) deposit_layer(rho32, std::true_type{});
+      else if (!crowded) deposit_layer(rho, std::false_type{});
+      else deposit_layer(rho, std::true_type{});
     }
-    };
-    if (narrow) deposit_layer(rho32);
-    else deposit_layer(rho);
     __syncthreads();
-    // planes completed by this layer
-    const int f0 = max(4 * sz - 1, pz0), f1 = min(4 * sz + 2, pz1 - 1);
-    const int nplanes = f1 - f0 + 1;
-    for (int i = threadIdx.x; i < nplanes * DF * DF; i += BLK) {
-      const int pz = f0 + i / (DF * DF), e = i % (DF * DF);
+    // planes 4 sz - 1 .. 4 sz + 2 are complete: write the owned ones, clear all (what the borders
+    // collect is never read)
+    for (int i = threadIdx.x; i < 4 * DF * DF; i += BLK) {
+      const int pl = i / (DF * DF), e = i % (DF * DF), pz = 4 * sz - 1 + pl;
       const int y = e / DF, x = e - y * DF;
-      const int idx = slot_of(pz) * DF * DF + e;
+      int sl = first + pl;
+      sl = sl >= NSLOT ? sl - NSLOT : sl;
+      const int idx = sl * PLANE + (y + 1) * PX + x + 1;
       double r;
       if (narrow) {
         r = (double)rho32[idx];
@@ -448,23 +530,24 @@ __device__ __forceinline__ void deposit_column(const DepArgs& a, const unsigned 
         r = (double)rho[idx];
         rho[idx] = 0ull;
       }
-      a.mesh[((int64_t)pz * a.nm + (4 * cy0 + y)) * a.pitch_f + (4 * cx0 + x)] = (float)(r * a.inv_mean - 1.0);
+      if (pz >= pz0 && pz < pz1)
+        a.mesh[((int64_t)pz * a.nm + (4 * cy0 + y)) * a.pitch_f + (4 * cx0 + x)] = (float)(r * a.inv_mean - 1.0);
     }
     __syncthreads();
   }
 }
 
-template <int NCHI, int BLK>
-__global__ __launch_bounds__(BLK) void k_deposit(DepArgs a) {
-  deposit_column<NCHI, BLK>(a, xcd_block(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y));
+template <int NCHI, int DTX, int BLK>
+__global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(8))) void k_deposit(DepArgs a) {
+  deposit_column<NCHI, DTX, BLK>(a, xcd_block(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y));
 }
 
 // every box of an ensemble in one launch (a box's workgroups: its columns times its z chunks)
-template <int NCHI, int BLK>
-__global__ __launch_bounds__(BLK) void k_deposit_boxes(BoxTable<DepArgs> t) {
+template <int NCHI, int DTX, int BLK>
+__global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(8))) void k_deposit_boxes(BoxTable<DepArgs> t) {
   const unsigned l = xcd_block(blockIdx.x, gridDim.x);
   const int b = box_of(t.first, t.nbox, l);
-  deposit_column<NCHI, BLK>(t.args[b], l - t.first[b]);
+  deposit_column<NCHI, DTX, BLK>(t.args[b], l - t.first[b]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2233,6 +2316,11 @@ __global__ void k_noise(float* out, int n, int64_t pitch_f, uint64_t seed) {
     else CALL(2, 2);                                                          \
   } while (0)
 
+// side of the deposit's columns in coarse cells: 8, where the ring is 36 cells to 64 and a workgroup of 16
+// wavefronts shares its planes; 4 in boxes of at most 32 cells a side, which have too few columns of 8
+// to fill the chip (16^3 cells 27 -> 14 us; with 64^3 cells columns of 4 take 232 us, of 8 135)
+static int deposit_dtx(const Sim& s) { return s.nc <= 32 ? 4 : 8; }
+
 // the deposit's arguments for the state of parity cur, and its grid (columns x z chunks)
 static DepArgs deposit_args(const Sim& s, int cur, dim3* grid) {
   DepArgs a;
@@ -2244,29 +2332,33 @@ static DepArgs deposit_args(const Sim& s, int cur, dim3* grid) {
   a.pitch_f = (int64_t)s.mesh_plan.row_floats();
   a.nm = s.nm;
   a.nc = s.nc;
-  a.nt = s.nc / DTX > 0 ? s.nc / DTX : 1;
-  // z chunks: enough workgroups to fill the chip, each chunk at least 4 coarse layers thick
-  const int cols = a.nt * a.nt;
-  int nchunk = 16384 / cols;
-  nchunk = nchunk < 1 ? 1 : (nchunk > s.nc / 4 ? s.nc / 4 : nchunk);
+  const int dtx = deposit_dtx(s), cols = (s.nc / dtx) * (s.nc / dtx);
+  // z chunks: about 2048 workgroups of 16 wavefronts are four rounds of the chip, and a chunk of zc layers
+  // reads zc + 2 (512^3 cells: 749 us; in 4096 chunks 809, in 8192 956); at least 4 layers, 2 in columns of 4
+  int nchunk = dtx == 8 ? 2048 / cols : s.nc / 2;
+  const int thin = dtx == 8 ? 4 : 2;
+  nchunk = nchunk < 1 ? 1 : (nchunk > s.nc / thin ? s.nc / thin : nchunk);
   a.zc = (s.nc + nchunk - 1) / nchunk;
   nchunk = (s.nc + a.zc - 1) / a.zc;
   a.inv_mean = (double)s.nm * (double)s.nm * (double)s.nm / ((double)s.n * ldexp(1.0, 3 * (8 * s.nchi - 1)));
-  a.interleave = s.deposit_variant & 1;
   *grid = dim3((unsigned)cols, (unsigned)nchunk);
   return a;
 }
 
+// the deposit kernel NAME for columns of dtx cells and nchi-byte positions
+#define CUBE_DEP(NAME, GRID, ARG)                                                          \
+  do {                                                                                     \
+    if (dtx == 4 && nchi == 1) NAME<1, 4, 256><<<GRID, 256, 0, st>>>(ARG);                  \
+    else if (dtx == 4) NAME<2, 4, 256><<<GRID, 256, 0, st>>>(ARG);                          \
+    else if (nchi == 1) NAME<1, 8, 1024><<<GRID, 1024, 0, st>>>(ARG);                       \
+    else NAME<2, 8, 1024><<<GRID, 1024, 0, st>>>(ARG);                                      \
+  } while (0)
+
 void launch_deposit(Sim& s, hipStream_t st) {
   dim3 grid;
   const DepArgs a = deposit_args(s, s.cur, &grid);
-  if (s.deposit_variant & 2) {
-    if (s.nchi == 1) k_deposit<1, 512><<<grid, 512, 0, st>>>(a);
-    else k_deposit<2, 512><<<grid, 512, 0, st>>>(a);
-  } else {
-    if (s.nchi == 1) k_deposit<1, 256><<<grid, 256, 0, st>>>(a);
-    else k_deposit<2, 256><<<grid, 256, 0, st>>>(a);
-  }
+  const int dtx = deposit_dtx(s), nchi = s.nchi;
+  CUBE_DEP(k_deposit, grid, a);
   CUBE_HIP(hipGetLastError());
 }
 
@@ -2516,23 +2608,20 @@ __global__ void k_step_end_boxes(const EndArgs* __restrict__ tab, int nbox) {
 void ensemble_deposit(EnsembleStep& es, const std::vector<Sim*>& boxes) {
   const EnsembleStep* e = &es;
   for (int nchi = 1; nchi <= 2; ++nchi)
-    for (int blk : {256, 512}) {
+    for (int dtx : {4, 8}) {
       std::vector<DepArgs> args;
       std::vector<uint32_t> per;
       for (Sim* s : boxes) {
-        if (s->nchi != nchi || ((s->deposit_variant & 2) ? 512 : 256) != blk) continue;
+        if (s->nchi != nchi || deposit_dtx(*s) != dtx) continue;
         dim3 g;
         args.push_back(deposit_args(*s, s->cur, &g));
         per.push_back(g.x * g.y);
       }
       if (args.empty()) continue;
-      const StagedBoxes g = stage_boxes(es, args, per, blk);
-      es.launches.push_back([e, g, nchi, blk](hipStream_t st) {
+      const StagedBoxes g = stage_boxes(es, args, per, dtx == 4 ? 256 : 1024);
+      es.launches.push_back([e, g, nchi, dtx](hipStream_t st) {
         const BoxTable<DepArgs> t = table_of<DepArgs>(e, g);
-        if (nchi == 1 && blk == 512) k_deposit_boxes<1, 512><<<g.blocks, 512, 0, st>>>(t);
-        else if (nchi == 1) k_deposit_boxes<1, 256><<<g.blocks, 256, 0, st>>>(t);
-        else if (blk == 512) k_deposit_boxes<2, 512><<<g.blocks, 512, 0, st>>>(t);
-        else k_deposit_boxes<2, 256><<<g.blocks, 256, 0, st>>>(t);
+        CUBE_DEP(k_deposit_boxes, g.blocks, t);
         CUBE_HIP(hipGetLastError());
       });
     }
