@@ -326,10 +326,22 @@ __global__ __launch_bounds__(256) void k_fft_x_c2r_boxes(float* const* __restric
 // ---- y / z passes: blocks of BX columns ------------------------------------------------------
 // BX: complex columns per workgroup (4 or 8 for N >= 1024, 8 or 16 below: 16 needs N <= 512 to
 // fit LDS). The padding of the rows leaves room for the widest.
+// Threads: a pass is bound by its loads in flight against two to five exchanges through LDS, so the
+// power-of-two sizes take as many threads as still keep two workgroups on a CU (the LDS holds two of
+// the widest blocks): values per thread N BX / BLOCK = 8 at 256 and 512, 16 at 1024. z pass with 256
+// threads before, in us: 512^3 width 16 352 -> 266, 1024^3 width 8 3350 -> 2850; 256^3 width 16 43 -> 41.
+// 1024 threads at 1024^3 need 71 registers, so one workgroup is left per CU (5050 us; held to 64 by
+// spilling, 3530); the sizes with a factor 3 are fastest with 256 (384^3 width 8: 142, with 384 threads
+// 176, with 192 155).
 template <int N, int BX>
 struct ColCfg {
   static constexpr int NQ = N * BX / 2;
-  static constexpr int BLOCK = (N >= 2048) ? (BX >= 8 ? 1024 : 512) : (NQ % 256 == 0 ? 256 : (NQ % 128 == 0 ? 128 : 64));
+  static constexpr int BLOCK = N >= 2048             ? (BX >= 8 ? 1024 : 512)
+                               : N == 1024           ? NQ / 8
+                               : N == 512 || N == 256 ? NQ / 4
+                               : NQ % 256 == 0       ? 256
+                               : NQ % 128 == 0       ? 128
+                                                     : 64;
 };
 constexpr int col_bx_default(int n) { return n >= 1024 ? 8 : 16; }
 constexpr int col_bx_pitch(int n) { return n >= 1024 ? 8 : 16; }
