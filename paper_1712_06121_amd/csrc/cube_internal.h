@@ -45,6 +45,13 @@ __host__ __device__ inline unsigned xcd_block(unsigned b, unsigned n) {
   return x * per + (x < rem ? x : rem) + i;
 }
 
+// the same ranges, each walked from its end
+__host__ __device__ inline unsigned xcd_block_back(unsigned b, unsigned n) {
+  const unsigned per = n / 8, rem = n % 8, x = b % 8, i = b / 8;
+  const unsigned more = x < rem ? 1u : 0u;
+  return x * per + (more ? x : rem) + (per + more - 1 - i);
+}
+
 // ---- ensemble launches: one launch of a stage over several boxes ----------------------------
 // The launch's logical workgroups (XCD-contiguous order) are cut into consecutive ranges, box b
 // owning [first[b], first[b + 1]); args[b] holds box b's kernel arguments. The box of a workgroup

@@ -190,6 +190,12 @@ __device__ __forceinline__ void fft_lds(float2* lds, const float2* __restrict__ 
 }
 
 // ---- x pass: real rows <-> half spectrum ---------------------------------------------------
+// Both x passes walk the mesh backwards and the passes next to them forwards (the deposit and the y
+// pass before and after the forward transform, the y pass and the particle kernels around the
+// inverse): a pass then starts on what its predecessor wrote or read last, which the last-level
+// cache (256 MB) still holds. 512^3 mesh (541 MB), one 512^3 solve: y forward 256 -> 193 us, y inverse
+// 212 -> 199, x inverse 239 -> 198, the five passes 1180 -> 1050 us. 256^3 (68 MB, held whole either
+// way) is unchanged; at 1024^3 (4.3 GB) 0.5 %.
 // rows per workgroup: the largest power of two with at most 2048 complex values in LDS that
 // divides the row count
 constexpr int rows_per_block(int n) {
@@ -299,27 +305,27 @@ __device__ __forceinline__ void fft_x_c2r_rows(float* __restrict__ data, int64_t
 template <int N>
 __global__ __launch_bounds__(256) void k_fft_x_r2c(float* __restrict__ data, int64_t pitch_f,
                                                   const float2* __restrict__ tw) {
-  fft_x_r2c_rows<N>(data, pitch_f, tw, xcd_block(blockIdx.x, gridDim.x));
+  fft_x_r2c_rows<N>(data, pitch_f, tw, xcd_block_back(blockIdx.x, gridDim.x));
 }
 
 template <int N>
 __global__ __launch_bounds__(256) void k_fft_x_c2r(float* __restrict__ data, int64_t pitch_f,
                                                   const float2* __restrict__ tw) {
-  fft_x_c2r_rows<N>(data, pitch_f, tw, xcd_block(blockIdx.x, gridDim.x));
+  fft_x_c2r_rows<N>(data, pitch_f, tw, xcd_block_back(blockIdx.x, gridDim.x));
 }
 
 // the x passes of several meshes of one size in one launch: per workgroups of each mesh, in order
 template <int N>
 __global__ __launch_bounds__(256) void k_fft_x_r2c_boxes(float* const* __restrict__ data, int64_t pitch_f,
                                                         const float2* __restrict__ tw, unsigned per) {
-  const unsigned l = xcd_block(blockIdx.x, gridDim.x);
+  const unsigned l = xcd_block_back(blockIdx.x, gridDim.x);
   fft_x_r2c_rows<N>(data[l / per], pitch_f, tw, l % per);
 }
 
 template <int N>
 __global__ __launch_bounds__(256) void k_fft_x_c2r_boxes(float* const* __restrict__ data, int64_t pitch_f,
                                                         const float2* __restrict__ tw, unsigned per) {
-  const unsigned l = xcd_block(blockIdx.x, gridDim.x);
+  const unsigned l = xcd_block_back(blockIdx.x, gridDim.x);
   fft_x_c2r_rows<N>(data[l / per], pitch_f, tw, l % per);
 }
 
