@@ -353,17 +353,32 @@ void ic_fields(Sim& s, float** psi, float** wk_out, std::vector<void*>& temps, b
   // i n_d tab[|n|^2] gives the displacement in fine cells after the unnormalised inverse FFT
   const int h = s.np / 2;
   const int64_t ntab = 3LL * h * h + 1;
-  std::vector<float> tab(ntab, 0.0f);
   const double box = s.p.box, np3 = (double)s.np * s.np * s.np;
   const double di = s.cosmo.D(s.p.a_init);
-  for (int64_t n2 = 1; n2 < ntab; ++n2) {
+  auto entry = [&](int64_t n2) {
     const double k = 2.0 * M_PI * std::sqrt((double)n2) / box;
     const double amp = std::sqrt(np3 * s.cosmo.pk_shape(k) * di * di / (box * box * box));
-    tab[n2] = (float)(amp * (double)s.nm / (2.0 * M_PI * (double)n2 * np3));
-  }
-  float* dtab = static_cast<float*>(s.dmalloc(sizeof(float) * ntab));
+    return (float)(amp * (double)s.nm / (2.0 * M_PI * (double)n2 * np3));
+  };
+  float* dtab = static_cast<float*>(s.dmalloc(sizeof(float) * ntab + sizeof(uint32_t) * (1 + kICNear)));
   temps.push_back(dtab);
-  CUBE_HIP(hipMemcpy(dtab, tab.data(), sizeof(float) * ntab, hipMemcpyHostToDevice));
+  uint32_t* near_dev = reinterpret_cast<uint32_t*>(dtab + ntab);
+  const Cosmo& co = s.cosmo;
+  launch_ic_table(ICTable{box, np3, di, co.amp, co.ns, co.om * co.h, (double)s.nm, ntab}, dtab, near_dev, s.stream);
+  std::vector<uint32_t> near_list(1 + kICNear);
+  CUBE_HIP(hipMemcpyAsync(near_list.data(), near_dev, sizeof(uint32_t) * near_list.size(), hipMemcpyDeviceToHost, s.stream));
+  CUBE_HIP(hipStreamSynchronize(s.stream));
+  const uint32_t nnear = near_list[0];
+  if (nnear <= kICNear) {
+    for (uint32_t i = 1; i <= nnear; ++i) {
+      const float v = entry(near_list[i]);
+      CUBE_HIP(hipMemcpy(dtab + near_list[i], &v, sizeof(float), hipMemcpyHostToDevice));
+    }
+  } else {
+    std::vector<float> tab(ntab, 0.0f);
+    for (int64_t n2 = 1; n2 < ntab; ++n2) tab[n2] = entry(n2);
+    CUBE_HIP(hipMemcpy(dtab, tab.data(), sizeof(float) * ntab, hipMemcpyHostToDevice));
+  }
   for (int d = 0; d < 3; ++d) fft_ic_component(s.lat_plan, wk, psi[d], dtab, d, s.stream);
   *wk_out = wk;
 }
@@ -420,7 +435,8 @@ int enqueue_steps(Sim& s, int k) {
 
 // Device bytes cube_create allocates for these parameters, plus the temporaries of
 // cube_init_ic (the transformed noise when the lattice and mesh sizes differ, the displacement
-// fields that do not fit in a particle buffer, the amplitude table). Mirrors the allocations of
+// fields that do not fit in a particle buffer, the amplitude table; its list of 1 KB is within the spare
+// bytes). Mirrors the allocations of
 // cube_create, ic_fields and fft_plan_create.
 int64_t footprint_bytes(const cube_params& p) {
   const int64_t nm = p.nm_side, nc = p.nc_side, np = p.np_side, nc3 = nc * nc * nc;

@@ -261,6 +261,15 @@ void cross_shells(const FFTPlan& pa, const float* a, const FFTPlan& pb, const fl
 void fft_ic_component(const FFTPlan& pl, const float* wk, float* out, const float* tab, int dim,
                       hipStream_t st);
 
+// The table tab[n2], n2 < ntab (entry 0: 0), in FP64 on the device. near_list gets the number of entries
+// whose FP64 value lies so close to the middle of two floats that the host's library, whose logarithm
+// and powers may round differently, could yield the other one, then (the first kICNear of) their indices.
+constexpr uint32_t kICNear = 255;
+struct ICTable {
+  double box, np3, di, amp, ns, omh, nm;
+  int64_t ntab;
+};
+void launch_ic_table(const ICTable& c, float* tab, uint32_t* near_list, hipStream_t st);
 void launch_noise(const FFTPlan& pl, float* out, uint64_t seed, hipStream_t st);
 void launch_deposit(Sim& s, hipStream_t st);
 // move: mode 0 = step (force from mesh), 1 = drift only (no force), 2 = initial conditions
