@@ -954,6 +954,9 @@ __device__ __forceinline__ int find_cell_in(const uint32_t* pre, int lo, int hi,
 // the stencils of a cell's particles over the LDS banks (8.0 cycles a read of 64 lanes on average
 // over uniform positions; 9.6 with 528).
 //
+// A tile's loads are in flight together: counts, potential, then, as soon as the counts are there, the
+// codes of each wavefront's first chunk, and one barrier for all of it (with the codes requested behind
+// that barrier 96^3 on 192^3 39 -> 36 us, 128^3 on 256^3 65 -> 62, 256^3 on 512^3 672 -> 660).
 // Two workgroups of 16 wavefronts share a CU (64 VGPRs; workgroups of 8 and 12 take 3 to 12% longer
 // where cells hold many particles). Before (512 threads, moments by wavefront prefix scans and device
 // atomics) and now: 512^3 particles on 512^3 cells 2291 -> 1647 us early, 2838 -> 1750 clustered, 374 vector
@@ -982,9 +985,14 @@ __device__ __forceinline__ void count_tile(MoveArgs a, const unsigned lb) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // own cell `lane`, in every wavefront: count and storage start
-  int ox, oy, oz;
-  tile_xyz(lane, ox, oy, oz);
-  const uint32_t oc = (uint32_t)(g.cx0 + ox) + (uint32_t)a.nc * ((uint32_t)(g.cy0 + oy) + (uint32_t)a.nc * (uint32_t)(g.cz0 + oz));
+  // (its index is formed anew where it is used next: kept, it is one register too many)
+  auto own_cell = [&] {
+    int l = lane, ox, oy, oz;
+    asm volatile("" : "+v"(l));
+    tile_xyz(l, ox, oy, oz);
+    return (uint32_t)(g.cx0 + ox) + (uint32_t)a.nc * ((uint32_t)(g.cy0 + oy) + (uint32_t)a.nc * (uint32_t)(g.cz0 + oz));
+  };
+  const uint32_t oc = own_cell();
   uint32_t cnt;
   uint64_t beg = 0;  // initial conditions: the lattice particles of a cell are numbered from 0
   if constexpr (MODE == 2) {
@@ -993,51 +1001,33 @@ __device__ __forceinline__ void count_tile(MoveArgs a, const unsigned lb) {
     cnt = a.cnt[oc];
     beg = a.off[oc];
   }
-  float tdec_r = 0.0f;
-  float4 cv_r = make_float4(0.f, 0.f, 0.f, 0.f);
-  if constexpr (MODE != 2) {
-    if (NNU == 1 && threadIdx.x < 255) tdec_r = a.tdec[threadIdx.x];
-    if (threadIdx.x < TC) cv_r = make_float4(a.vc[oc], (a.vc + a.nc3)[oc], (a.vc + 2 * a.nc3)[oc], a.vs[oc]);
-  }
+  // Potential: every load of the tile in flight at once, in this order without a branch around them (past
+  // the end a load repeats the last row's), so that waiting for the counts does not wait for them. A thread
+  // loads the same quad of x in rows 170 apart (7 planes and 16 rows)
+  constexpr uint32_t QX = CPX / 4, NR = PH * PH, RPK = CNTH / QX, NL = (NR + RPK - 1) / RPK;
+  typedef float quad __attribute__((ext_vector_type(4)));  // (an array of float4 goes to scratch memory here)
+  quad stage[MODE == 0 ? NL : 1];
+  const uint32_t r0 = min(threadIdx.x / QX, RPK - 1u), qx = threadIdx.x % QX;
   if constexpr (MODE == 0) {
-    // every load of the tile in flight at once; z and y wrap only in the tiles at the box's faces
-    constexpr uint32_t QX = CPX / 4, NQ = PH * PH * QX, NL = (NQ + CNTH - 1) / CNTH;
-    typedef float quad __attribute__((ext_vector_type(4)));  // (an array of float4 goes to scratch memory here)
-    quad stage[NL];
-    const int fx0 = 4 * (g.cx0 - 1), fy0 = 4 * g.cy0 - 3, fz0 = 4 * g.cz0 - 3;
-    const bool inner = fx0 >= 0 && fy0 >= 0 && fz0 >= 0 && fx0 + CPX <= a.nm && fy0 + PH <= a.nm && fz0 + PH <= a.nm;
-    const uint32_t nmu = (uint32_t)a.nm, pitch = (uint32_t)a.pitch_f;
-    if (inner) {
-      const float* const src = a.mesh + ((int64_t)fz0 * nmu + fy0) * pitch + fx0;
-#pragma unroll
-      for (uint32_t k = 0; k < NL; ++k) {
-        const uint32_t e = threadIdx.x + k * CNTH;
-        if (e < NQ) {
-          // 22 planes of at most 2048 rows of 2064 floats: below 2^27 floats from the first
-          const uint32_t r = e / QX, j = e - r * QX, z = r / PH, y = r - z * PH;
-          stage[k] = *reinterpret_cast<const quad*>(src + (__umul24(__umul24(z, nmu) + y, pitch) + 4u * j));
-        }
-      }
-    } else {
-#pragma unroll
-      for (uint32_t k = 0; k < NL; ++k) {
-        const uint32_t e = threadIdx.x + k * CNTH;
-        if (e < NQ) {
-          const uint32_t r = e / QX, j = e - r * QX, z = r / PH, y = r - z * PH;
-          const int gx = wrapi(fx0 + 4 * (int)j, a.nm), gy = wrapi(fy0 + (int)y, a.nm), gz = wrapi(fz0 + (int)z, a.nm);
-          stage[k] = *reinterpret_cast<const quad*>(a.mesh + ((int64_t)gz * a.nm + gy) * a.pitch_f + gx);
-        }
-      }
-    }
+    const uint32_t gx = (uint32_t)wrapi(4 * (g.cx0 - 1) + 4 * (int)qx, a.nm);
+    uint32_t z = r0 / PH, y = r0 - z * PH;
 #pragma unroll
     for (uint32_t k = 0; k < NL; ++k) {
-      const uint32_t e = threadIdx.x + k * CNTH;
-      if (e < NQ) *reinterpret_cast<quad*>(&ph[4 * e + (CPP - PH * CPX) * (e / (PH * QX))]) = stage[k];
+      if (k) {
+        z += RPK / PH;
+        y += RPK % PH;
+        if (y >= (uint32_t)PH) {
+          y -= PH;
+          ++z;
+        }
+        if (k == NL - 1 && z >= (uint32_t)PH) {
+          z = PH - 1;
+          y = PH - 1;
+        }
+      }
+      const uint32_t gy = (uint32_t)wrapi(4 * g.cy0 - 3 + (int)y, a.nm), gz = (uint32_t)wrapi(4 * g.cz0 - 3 + (int)z, a.nm);
+      stage[k] = *reinterpret_cast<const quad*>(a.mesh + ((uint64_t)(__umul24(gz, (uint32_t)a.nm) + gy) * (uint32_t)a.pitch_f + gx));
     }
-  }
-  if constexpr (MODE != 2) {
-    if (NNU == 1 && threadIdx.x < 255) tdec_lds[threadIdx.x] = tdec_r;
-    if (threadIdx.x < TC) cellv[threadIdx.x] = cv_r;
   }
   for (int i = threadIdx.x; i < 2 * CSLOT; i += CNTH) reinterpret_cast<uint4*>(mom)[i] = make_uint4(0u, 0u, 0u, 0u);
   for (int i = threadIdx.x; i < TC * 27 / 4; i += CNTH) reinterpret_cast<uint4*>(left)[i] = make_uint4(0u, 0u, 0u, 0u);
@@ -1047,16 +1037,15 @@ __device__ __forceinline__ void count_tile(MoveArgs a, const unsigned lb) {
   const uint64_t rel = beg - (inc - cnt);  // storage index of a cell's particle i of the tile: rel + i
   const uint32_t rel_lo = (uint32_t)rel, rel_hi = (uint32_t)(rel >> 32);
   const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-  __syncthreads();
   const float* const tdec = NNU == 1 ? tdec_lds : a.tdec;
   const float unit = (float)(1.0 / (double)(1 << SH));
 
   // cell and storage index of each lane's particle of the chunk at c0 (lanes past the end: the tile's
   // last particle)
   auto locate = [&](uint32_t c0, int& sc, int64_t& p) {
-    int q = __popcll(__ballot(inc <= c0));  // the cell of the chunk's first particle
+    int q = min((int)__popcll(__ballot(inc <= c0)), 63);  // the cell of the chunk's first particle
     uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)inc, q);
-    const uint32_t i = min(c0 + (uint32_t)lane, tot - 1u);
+    const uint32_t i = min(c0 + (uint32_t)lane, max(tot, 1u) - 1u);
     sc = q;
     uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)rel_lo, q), hi = (uint32_t)__builtin_amdgcn_readlane((int)rel_hi, q);
     const uint32_t stop = min(c0 + 64u, tot);
@@ -1071,13 +1060,38 @@ __device__ __forceinline__ void count_tile(MoveArgs a, const unsigned lb) {
         hi = qh;
       }
     }
-    p = (int64_t)((((uint64_t)hi << 32) | lo) + i);
+    p = tot ? (int64_t)((((uint64_t)hi << 32) | lo) + i) : 0;
   };
 
   float vmax = 0.0f, gmax = 0.0f;  // largest |v|^2 and |t|^2 of this lane's particles
   Codes<NCHI, NNU> wn{0u, 0u, 0u, 0u};
   int sn = 0;
   int64_t pn = 0;
+  // the codes of the first chunk are requested before the potential has arrived (wavefronts without a
+  // chunk request the codes of the tile's last particle or, of an empty tile, of storage's first)
+  uint32_t c0 = 64u * (uint32_t)wave;
+  if constexpr (MODE == 2) {
+    if (c0 < tot) locate(c0, sn, pn);
+  } else {
+    locate(min(c0, max(tot, 1u) - 1u), sn, pn);
+    wn.load(a.codes, a.cap, pn);
+    if (NNU == 1 && threadIdx.x < 255) tdec_lds[threadIdx.x] = a.tdec[threadIdx.x];
+    if (threadIdx.x < TC) {
+      const uint32_t c = own_cell();
+      cellv[threadIdx.x] = make_float4(a.vc[c], (a.vc + a.nc3)[c], (a.vc + 2 * a.nc3)[c], a.vs[c]);
+    }
+  }
+  if constexpr (MODE == 0) {
+    if (threadIdx.x < QX * RPK) {
+#pragma unroll
+      for (uint32_t k = 0; k < NL; ++k) {
+        const uint32_t r = r0 + k * RPK;  // plane r / PH by a reciprocal that holds up to NR
+        if (k < NL - 1 || r < NR)
+          *reinterpret_cast<quad*>(&ph[__umul24(r, CPX) + (CPP - PH * CPX) * (__umul24(r, 65536 / PH + 1) >> 16) + 4u * qx]) = stage[k];
+      }
+    }
+  }
+  __syncthreads();
   auto chunk = [&](auto full, uint32_t c0) {
     constexpr bool FULL = decltype(full)::value;
     const int s = sn;
@@ -1201,11 +1215,6 @@ __device__ __forceinline__ void count_tile(MoveArgs a, const unsigned lb) {
       if (!stay) atomicAdd(&left[s * 27 + dcode], 1u);
     }
   };
-  uint32_t c0 = 64u * (uint32_t)wave;
-  if (c0 < tot) {
-    locate(c0, sn, pn);
-    if constexpr (MODE != 2) wn.load(a.codes, a.cap, pn);
-  }
   for (; c0 + 64u <= tot; c0 += 64u * NW) chunk(std::true_type{}, c0);
   if (c0 < tot) chunk(std::false_type{}, c0);
   if constexpr (MEAS) {
@@ -1237,11 +1246,14 @@ __device__ __forceinline__ void count_tile(MoveArgs a, const unsigned lb) {
   }
   // counts: a wavefront writes one displacement of all own cells, a lane per cell; the wavefront that
   // has displacement 13 takes the leavers from the cell's count
-  uint32_t* const col = a.mig + oc;
+  uint32_t* const col = a.mig + own_cell();
   for (int d = wave; d < 27; d += NW) {
-    uint32_t n = d == 13 ? cnt : left[lane * 27 + d];
-    if (d == 13)
+    uint32_t n = left[lane * 27 + d];
+    if (d == 13) {
+      const uint32_t below = (uint32_t)__shfl_up((int)inc, 1);
+      n = inc - (lane ? below : 0u);  // the cell's count
       for (int j = 0; j < 27; ++j) n -= left[lane * 27 + j];  // entry 13 stays 0
+    }
     (col + d * a.nc3)[0] = n;
   }
 }
