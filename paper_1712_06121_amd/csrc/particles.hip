@@ -2047,6 +2047,12 @@ __device__ __forceinline__ double u128_to_double(unsigned long long hi, unsigned
   return ldexp((double)(keep | (lost != 0ull ? 1ull : 0ull)), s);
 }
 
+// the global dispersion from the 128-bit sum of its terms
+__device__ __forceinline__ double global_sg2(unsigned long long hi, unsigned long long lo, int64_t n) {
+  const double sg2 = u128_to_double(hi, lo) / ((3.0 * (double)n) * 1048576.0);
+  return sg2 > 0.0 ? sg2 : 8.673617379884035e-19;  // 2^-60
+}
+
 // single workgroup: exclusive scan of the per-block counts; the global dispersion, the exact sum of
 // the per-block int64 terms (each in [0, 2^62)) in 128 bits
 struct ScanArgs {
@@ -2106,9 +2112,7 @@ __device__ __forceinline__ void scan_blocks(const ScanArgs& a) {
     for (int w = 0; w < 16; ++w) total += wtot[w];
     *a.off_end = total;
     if ((int64_t)total != a.n_expect) atomicOr(a.flags, FLAG_COUNT);
-    double sg2 = u128_to_double(qh[0], ql[0]) / ((3.0 * (double)a.n_expect) * 1048576.0);
-    if (!(sg2 > 0.0)) sg2 = 8.673617379884035e-19;  // 2^-60
-    a.scal[0] = sg2;
+    a.scal[0] = global_sg2(qh[0], ql[0], a.n_expect);
   }
 }
 
@@ -2119,12 +2123,17 @@ __global__ __launch_bounds__(1024) void k_scan_blocks_boxes(const ScanArgs* __re
   scan_blocks(tab[blockIdx.x]);
 }
 
+// Up to this many link blocks (64^3 cells) every finalize block reads all their counts and terms itself;
+// above, k_scan_blocks goes before. A launch less against 16 bytes per pair of blocks from L2; link, scan
+// and finalize together in us, with the scan and without: 16^3 cells 17.0 and 13.6, 48^3 20.2 and 17.5, 64^3
+// 27.0 and 25.3, 96^3 87 and 92, 128^3 179 and 230.
+constexpr int64_t kScanOwn = 1024;
+
 struct FinArgs {
   const uint32_t* cnt_n;
-  const uint64_t* blk_off;
+  ScanArgs scan;
   uint64_t* off_n;
   const double* dev;
-  const double* scal;
   float* vs_n;
   float* vinv;
   int64_t nc3;
@@ -2136,13 +2145,53 @@ struct FinArgs {
 __device__ __forceinline__ void finalize_block(const FinArgs& a, const unsigned blk) {
   __shared__ uint32_t pre[LINK_BLK + 1];
   __shared__ uint32_t wsum[LINK_BLK / 64];
+  __shared__ unsigned long long own[4][LINK_BLK / 64];
   if (workgroup_step_failed(a.flags)) return;
   const int64_t c = (int64_t)blk * LINK_BLK + threadIdx.x;
   const uint32_t n = (c < a.nc3) ? a.cnt_n[c] : 0u;
-  block_exclusive_scan(n, pre, LINK_BLK, wsum);
+  const ScanArgs& g = a.scan;
+  unsigned long long off;
+  double sg2;
+  if (g.nblk <= kScanOwn) {
+    // particles before this block, all of them, and the dispersion terms' two halves: sums of at most
+    // kScanOwn values of 32 bits each
+    unsigned long long v[4] = {0, 0, 0, 0};
+    for (uint32_t b = threadIdx.x; b < (uint32_t)g.nblk; b += LINK_BLK) {
+      const unsigned long long nb = g.blk_n[b], q = (unsigned long long)g.blk_q[b];
+      v[0] += b < blk ? nb : 0ull;
+      v[1] += nb;
+      v[2] += q & 0xffffffffull;
+      v[3] += q >> 32;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const unsigned long long w = wave_sum_u64(v[k]);
+      if ((threadIdx.x & 63) == 0) own[k][threadIdx.x >> 6] = w;
+    }
+    block_exclusive_scan(n, pre, LINK_BLK, wsum);  // (has the barriers that `own` needs)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      v[k] = 0;
+#pragma unroll
+      for (int w = 0; w < LINK_BLK / 64; ++w) v[k] += own[k][w];
+    }
+    const unsigned long long lo = (v[3] << 32) + v[2];
+    sg2 = global_sg2((v[3] >> 32) + (lo < v[2] ? 1ull : 0ull), lo, g.n_expect);
+    off = v[0];
+    const bool bad = (int64_t)v[1] != g.n_expect;
+    if (blk == 0 && threadIdx.x == 0) {
+      *g.off_end = v[1];
+      g.scal[0] = sg2;
+      if (bad) atomicOr(g.flags, FLAG_COUNT);
+    }
+    if (bad) return;
+  } else {
+    block_exclusive_scan(n, pre, LINK_BLK, wsum);
+    off = g.blk_off[blk];
+    sg2 = g.scal[0];
+  }
   if (c >= a.nc3) return;
-  a.off_n[c] = a.blk_off[blk] + pre[threadIdx.x];
-  const double sg2 = a.scal[0];
+  a.off_n[c] = off + pre[threadIdx.x];
   double s2c = sg2;
   if (a.sigma_mode == CUBE_SIGMA_PER_CELL) {
     s2c = a.dev[c] / 3.0;
@@ -2427,10 +2476,9 @@ static ScanArgs scan_args(const Sim& s, int nxt) {
 static FinArgs fin_args(const Sim& s, int nxt) {
   FinArgs f;
   f.cnt_n = s.cnt[nxt];
-  f.blk_off = s.blk_off;
+  f.scan = scan_args(s, nxt);
   f.off_n = s.off[nxt];
   f.dev = s.dev;
-  f.scal = s.scal;
   f.vs_n = s.vs[nxt];
   f.vinv = s.vinv;
   f.nc3 = s.nc3;
@@ -2443,8 +2491,10 @@ static FinArgs fin_args(const Sim& s, int nxt) {
 static void link_scan_finalize(Sim& s, int nxt, const uint32_t* cnt_direct, hipStream_t st) {
   k_link<<<(unsigned)s.nblk, LINK_BLK, 0, st>>>(link_args(s, nxt, cnt_direct));
   CUBE_HIP(hipGetLastError());
-  k_scan_blocks<<<1, 1024, 0, st>>>(scan_args(s, nxt));
-  CUBE_HIP(hipGetLastError());
+  if (s.nblk > kScanOwn) {
+    k_scan_blocks<<<1, 1024, 0, st>>>(scan_args(s, nxt));
+    CUBE_HIP(hipGetLastError());
+  }
   k_finalize<<<(unsigned)s.nblk, LINK_BLK, 0, st>>>(fin_args(s, nxt));
   CUBE_HIP(hipGetLastError());
 }
@@ -2712,19 +2762,21 @@ void ensemble_move(EnsembleStep& es, const std::vector<Sim*>& boxes) {
   for (Sim* s : boxes) {
     const int nxt = s->cur ^ 1;
     la.push_back(link_args(*s, nxt, nullptr));
-    sa.push_back(scan_args(*s, nxt));
+    if (s->nblk > kScanOwn) sa.push_back(scan_args(*s, nxt));
     fa.push_back(fin_args(*s, nxt));
     per.push_back((uint32_t)s->nblk);
   }
   const StagedBoxes gl = stage_boxes(es, la, per, LINK_BLK);
   const StagedBoxes gf = stage_boxes(es, fa, per, LINK_BLK);
   const size_t os = es.put(sa);
-  const unsigned nbox = (unsigned)boxes.size();
-  es.launches.push_back([e, gl, gf, os, nbox](hipStream_t st) {
+  const unsigned nscan = (unsigned)sa.size();
+  es.launches.push_back([e, gl, gf, os, nscan](hipStream_t st) {
     k_link_boxes<<<gl.blocks, LINK_BLK, 0, st>>>(table_of<LinkArgs>(e, gl));
     CUBE_HIP(hipGetLastError());
-    k_scan_blocks_boxes<<<nbox, 1024, 0, st>>>(e->at<ScanArgs>(os));
-    CUBE_HIP(hipGetLastError());
+    if (nscan) {
+      k_scan_blocks_boxes<<<nscan, 1024, 0, st>>>(e->at<ScanArgs>(os));
+      CUBE_HIP(hipGetLastError());
+    }
     k_finalize_boxes<<<gf.blocks, LINK_BLK, 0, st>>>(table_of<FinArgs>(e, gf));
     CUBE_HIP(hipGetLastError());
   });
