@@ -104,23 +104,6 @@ void build_tables(Sim& s) {
     if ((double)f < e) f = std::nextafterf(f, INFINITY);
     s.h_tedge[j + half - 1] = f;
   }
-  // bucket table: t = u / (1 + |u|) in (-1, 1) split into 4 (M + 1) buckets; each holds the code of
-  // the bucket's lower end. Only a starting guess: the kernels finish with exact edge comparisons.
-  s.nbucket = 4 * (m + 1);
-  std::vector<int16_t> lo(s.nbucket);
-  for (int b = 0; b < s.nbucket; ++b) {
-    const double t = -1.0 + 2.0 * b / s.nbucket;
-    const double u = b == 0 ? -INFINITY : t / (1.0 - std::fabs(t));
-    const int cnt = (int)(std::upper_bound(s.h_tedge.begin(), s.h_tedge.end(), u,
-                                           [](double a, float e) { return a < (double)e; }) - s.h_tedge.begin());
-    lo[b] = (int16_t)(cnt - half);
-  }
-  // the move kernels rely on at most one edge per bucket (two exact steps then finish the search):
-  // consecutive lower-end codes differ by at most one
-  for (int b = 1; b < s.nbucket; ++b)
-    if (lo[b] - lo[b - 1] > 1) throw Error{CUBE_E_INVALID, "velocity bucket table holds two edges in one bucket"};
-  s.tbucket = static_cast<int16_t*>(s.dmalloc(sizeof(int16_t) * s.nbucket));
-  CUBE_HIP(hipMemcpy(s.tbucket, lo.data(), sizeof(int16_t) * s.nbucket, hipMemcpyHostToDevice));
   s.tdec = static_cast<float*>(s.dmalloc(sizeof(float) * m));
   // device edge table with sentinels: ext[0] = -inf, ext[i] = E[i - 1], ext[M] = +inf, so code nu
   // is the one with ext[nu + h] <= u < ext[nu + h + 1] for every u, end codes included

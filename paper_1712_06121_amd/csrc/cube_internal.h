@@ -156,8 +156,6 @@ struct Sim {
   // codec tables (device)
   float* tdec = nullptr;   // M entries
   float* tedge = nullptr;  // M + 1 entries: -inf, the M - 1 edges of Eq. (nu), +inf
-  int16_t* tbucket = nullptr;  // first guess of the velocity code per bucket of u / (1 + |u|)
-  int nbucket = 0;
   std::vector<float> h_tdec, h_tedge;
   int vm = 255;
   int ic_parent_np = 0;  // initial conditions refined from an ic_parent_np^3 parent (0: none)

@@ -572,8 +572,6 @@ struct MoveArgs {
   float kf, df;
   const float* tdec;
   const float* tedge;  // edge table with -inf / +inf sentinels (M + 1 entries)
-  const int16_t* tbucket;
-  int nbucket;
   int vhalf;
   uint32_t* mig;  // per (displacement, source cell): counts after the count pass, slots after the link
   int64_t* mom;   // count pass: four moments per cell of a tile and its ring, a block per tile
@@ -1271,27 +1269,45 @@ __global__ __launch_bounds__(CNTH) __attribute__((amdgpu_waves_per_eu(8))) void 
   count_tile<NCHI, NNU, 0, false>(t.args[b], l - t.first[b]);
 }
 
-// Eq. (nu) by the edge table: the code nu with ext[nu + h] <= u < ext[nu + h + 1] (h = (M-1)/2;
-// ext is the edge table with -inf and +inf at its ends), i.e. -h + #{edges <= u}. A bucket table
-// over t = u / (1 + |u|) gives the code at the lower end of the bucket. Every bucket holds at most
-// one edge (checked when the tables are built) and t, from an approximate reciprocal, is off by
-// far less than a bucket width, so the bucket found is the right one or a neighbour and the start
-// is within two codes of the answer; each exact step moves one code towards it, so two steps
-// reach it. With CHECKED, loops behind them (then never entered) keep the result exact whatever
-// the start. The sentinels keep every read inside the table, NaN included.
-template <bool CHECKED, typename BT>
-__device__ __forceinline__ int encode_nu(float u, const float* ext, const BT* bucket, int nbucket, int vhalf) {
-  const float t = u * __builtin_amdgcn_rcpf(1.0f + fabsf(u));
-  int b = (int)((t + 1.0f) * (0.5f * (float)nbucket));
-  b = b < 0 ? 0 : (b > nbucket - 1 ? nbucket - 1 : b);
-  int nu = bucket[b];
+// Eq. (nu): the codes nu with ext[nu + h] <= u < ext[nu + h + 1] (h = (M-1)/2; ext is the edge table with
+// -inf and +inf at its ends). x = (M / pi) atan(u) in FP32 (atan z = z P(z^2) on [0, 1], eight
+// coefficients fitted to 4e-8; M / 2 - x(1 / u) beyond) is off by at most 2e-5 codes for M = 255 and 0.005
+// for M = 65535 (over every edge, its neighbours and 2e7 other floats, the reciprocal up to an ulp off). So
+// the nearest integer is the code unless x lies close to the middle of two, where the table decides:
+// 0.02 and 2.4 in a hundred. Against a bucket table, whose entry two exact steps then corrected (five
+// reads a code in a chain of three, of 768 KB of tables for M = 65535), k_place takes, in us: 2-byte codes
+// and IDs, 96^3 on 192^3, 46 -> 21 (clustered 72 -> 38); 1-byte codes 128^3 on 256^3 34 -> 32, 256^3 on 256^3
+// clustered 239 -> 227.
+template <int NNU>
+__device__ __forceinline__ void encode_nu3(const float* u, const float* ext, int vhalf, int* nu) {
+  constexpr float M = NNU == 1 ? 255.0f : 65535.0f, H = 0.5f * (M - 1.0f);
+  constexpr double mp = (NNU == 1 ? 255.0 : 65535.0) / 3.14159265358979323846;
+  constexpr float sure = 0.5f - (NNU == 1 ? 1e-4f : 0.012f);
+  constexpr float c[8] = {(float)(0.9999993443489075 * mp),   (float)(-0.33329859375953674 * mp),
+                          (float)(0.19946563243865967 * mp),  (float)(-0.13908620178699493 * mp),
+                          (float)(0.09642171859741211 * mp),  (float)(-0.05591198801994324 * mp),
+                          (float)(0.021862726658582687 * mp), (float)(-0.004054504446685314 * mp)};
+  bool near = false;
 #pragma unroll
-  for (int r = 0; r < 2; ++r) nu += (int)(u >= ext[nu + vhalf + 1]) - (int)(u < ext[nu + vhalf]);
-  if constexpr (CHECKED) {
-    while (u >= ext[nu + vhalf + 1]) ++nu;
-    while (u < ext[nu + vhalf]) --nu;
+  for (int d = 0; d < 3; ++d) {
+    const float a = fabsf(u[d]);
+    const float z = fminf(a, __builtin_amdgcn_rcpf(a)), w = z * z;
+    float p = c[7];
+#pragma unroll
+    for (int k = 6; k >= 0; --k) p = __builtin_fmaf(p, w, c[k]);
+    const float zp = z * p;
+    const float x = copysignf(a > 1.0f ? 0.5f * M - zp : zp, u[d]);
+    const float r = rintf(x);
+    near = near | !(fabsf(x - r) <= sure);
+    nu[d] = (int)fminf(fmaxf(r, -H), H);  // (NaN: -h)
   }
-  return nu;
+  if (near) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const float* const e = ext + (nu[d] + vhalf);
+      nu[d] = min(nu[d] + (int)(u[d] >= e[1]) - (int)(u[d] < e[0]), vhalf);
+    }
+  }
 }
 
 template <int NCHI, int NNU, int MODE, int NTH>
@@ -1303,7 +1319,6 @@ __device__ __forceinline__ void move_scatter_tile(MoveArgs a, const unsigned lb)
   __shared__ uint64_t start[TC];
   __shared__ uint32_t wsum[NTH / 64];
   __shared__ float edges_lds[NNU == 1 ? 256 : 1];
-  __shared__ int16_t bucket_lds[NNU == 1 ? 1024 : 1];
   // the flag word is requested first and tested after the set-up (the last barrier): a wave that
   // returns then cannot hold up the others
   const uint32_t failed = __atomic_load_n(a.flags, __ATOMIC_RELAXED);
@@ -1311,12 +1326,9 @@ __device__ __forceinline__ void move_scatter_tile(MoveArgs a, const unsigned lb)
   load_potential<MODE, NTH>(a, ph, g);
   for (int i = threadIdx.x; i < TC * 27; i += NTH) grp[i] = 0u;
   const int nedge = 2 * a.vhalf + 2;
-  if constexpr (NNU == 1) {
+  if constexpr (NNU == 1)
     for (int i = threadIdx.x; i < nedge; i += NTH) edges_lds[i] = a.tedge[i];
-    for (int i = threadIdx.x; i < a.nbucket; i += NTH) bucket_lds[i] = a.tbucket[i];
-  }
   const float* edges = (NNU == 1) ? edges_lds : a.tedge;
-  const int16_t* bucket = (NNU == 1) ? bucket_lds : a.tbucket;
   const uint32_t total = own_cells<MODE>(a, g, pre, start, wsum);
   if (__builtin_amdgcn_readfirstlane(failed)) return;  // a failed step is not applied
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1364,12 +1376,11 @@ __device__ __forceinline__ void move_scatter_tile(MoveArgs a, const unsigned lb)
       const uint64_t dst = a.off_n[cn] + a.mig[(int64_t)dcode * a.nc3 + co] + gbase + (uint32_t)rin;
       if (dst < (uint64_t)a.cap) {
         const float inv = a.vinv[cn];
+        float u[3];
         int nu[3];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          const float u = (m.v[d] - a.vc_n[d * a.nc3 + cn]) * inv;
-          nu[d] = encode_nu<false>(u, edges, bucket, a.nbucket, a.vhalf);
-        }
+        for (int d = 0; d < 3; ++d) u[d] = (m.v[d] - a.vc_n[d * a.nc3 + cn]) * inv;
+        encode_nu3<NNU>(u, edges, a.vhalf, nu);
         Codes<NCHI, NNU> w;
         w.set(m.chi, nu);
         w.store(a.codes_n, a.cap, (int64_t)dst);
@@ -1417,7 +1428,6 @@ __device__ __forceinline__ void scatter_dense_tile(MoveArgs a, const unsigned lb
   __shared__ uint32_t wsum[NTH / 64];
   __shared__ float tdec_lds[NNU == 1 ? 255 : 1];
   __shared__ float edges_lds[NNU == 1 ? 256 : 1];
-  __shared__ int8_t bucket_lds[NNU == 1 ? 1024 : 1];  // 1-byte codes fit int8
   const TileGeom g = tile_of(lb, a.nt);
   // the flag word is requested first and tested after the set-up (the last barrier)
   const uint32_t failed = __atomic_load_n(a.flags, __ATOMIC_RELAXED);
@@ -1429,11 +1439,9 @@ __device__ __forceinline__ void scatter_dense_tile(MoveArgs a, const unsigned lb
     // starts, mean velocities and decode scales, then the potential tile
     static_assert(NTH >= 1024 && NTH >= TC, "one table entry and at most one own cell per thread");
     float tdec_r = 0.0f, edge_r = 0.0f;
-    int bucket_r = 0;
     if constexpr (NNU == 1) {
       if (threadIdx.x < 255) tdec_r = a.tdec[threadIdx.x];
       if (threadIdx.x < 256) edge_r = a.tedge[threadIdx.x];
-      if ((int)threadIdx.x < a.nbucket) bucket_r = a.tbucket[threadIdx.x];
     }
     float4 cv_r = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     uint64_t start_r = 0;
@@ -1448,7 +1456,6 @@ __device__ __forceinline__ void scatter_dense_tile(MoveArgs a, const unsigned lb
     if constexpr (NNU == 1) {
       if (threadIdx.x < 255) tdec_lds[threadIdx.x] = tdec_r;
       if (threadIdx.x < 256) edges_lds[threadIdx.x] = edge_r;
-      if ((int)threadIdx.x < a.nbucket) bucket_lds[threadIdx.x] = (int8_t)bucket_r;
     }
     if (threadIdx.x < TC) {
       cellv[threadIdx.x] = cv_r;
@@ -1496,10 +1503,6 @@ __device__ __forceinline__ void scatter_dense_tile(MoveArgs a, const unsigned lb
   if (threadIdx.x == 0) turn[0] = turn[1] = 0u;
   const float* tdec = NNU == 1 ? tdec_lds : a.tdec;
   const float* edges = NNU == 1 ? edges_lds : a.tedge;
-  using BT = std::conditional_t<NNU == 1, int8_t, int16_t>;
-  const BT* bucket;
-  if constexpr (NNU == 1) bucket = bucket_lds;
-  else bucket = a.tbucket;
   block_exclusive_scan(cnt_r, pre, TC, wsum);  // ends with a barrier
   if (__builtin_amdgcn_readfirstlane(failed)) return;  // a failed step is not applied
   const int lane = threadIdx.x & 63;
@@ -1676,12 +1679,11 @@ __device__ __forceinline__ void scatter_dense_tile(MoveArgs a, const unsigned lb
         if (active) {
           const uint64_t dst = dbase + b0 + rin;
           if (dst < (uint64_t)a.cap) {
+            float u[3];
             int nu[3];
 #pragma unroll
-            for (int d = 0; d < 3; ++d) {
-              const float u = (v[d] - vcn[d]) * inv;
-              nu[d] = encode_nu<false>(u, edges, bucket, a.nbucket, a.vhalf);
-            }
+            for (int d = 0; d < 3; ++d) u[d] = (v[d] - vcn[d]) * inv;
+            encode_nu3<NNU>(u, edges, a.vhalf, nu);
             Codes<NCHI, NNU> w;
             w.set(cq, nu);
             w.store(a.codes_n, a.cap, (int64_t)dst);
@@ -1729,7 +1731,6 @@ __device__ __forceinline__ void place_tile(const MoveArgs& a, const unsigned lb)
   __shared__ uint32_t offr[RC];       // of the tile's and ring's new cells: offset,
   __shared__ float4 stat[RC];         // mean velocity and encode scale
   __shared__ float edges_lds[NNU == 1 ? 256 : 1];
-  __shared__ int8_t bucket_lds[NNU == 1 ? 1024 : 1];
   const uint32_t failed = __atomic_load_n(a.flags, __ATOMIC_RELAXED);
   const TileGeom g = tile_of(lb, a.nt);
   const int lane = threadIdx.x & 63;
@@ -1768,13 +1769,8 @@ __device__ __forceinline__ void place_tile(const MoveArgs& a, const unsigned lb)
   if constexpr (NNU == 1) {
     static_assert(PLACE_BLK == 256, "one edge per thread");
     edges_lds[threadIdx.x] = a.tedge[threadIdx.x];
-    for (int i = threadIdx.x; i < a.nbucket; i += PLACE_BLK) bucket_lds[i] = (int8_t)a.tbucket[i];
   }
   const float* const edges = NNU == 1 ? edges_lds : a.tedge;
-  using BT = std::conditional_t<NNU == 1, int8_t, int16_t>;
-  const BT* bucket;
-  if constexpr (NNU == 1) bucket = bucket_lds;
-  else bucket = a.tbucket;
   __syncthreads();
   if (__builtin_amdgcn_readfirstlane(failed)) return;  // a failed step is not applied
   const int rbase = (ox + 1) + RG * (oy + 1) + RG * RG * (oz + 1);  // ring index of own cell `lane`
@@ -1863,8 +1859,7 @@ __device__ __forceinline__ void place_tile(const MoveArgs& a, const unsigned lb)
     dst = min(dst, (uint32_t)a.cap - 1u);
     const float u[3] = {(rc.x - st.x) * st.w, (rc.y - st.y) * st.w, (rc.z - st.z) * st.w};
     int nu[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) nu[d] = encode_nu<false>(u[d], edges, bucket, a.nbucket, a.vhalf);
+    encode_nu3<NNU>(u, edges, a.vhalf, nu);
     Codes<NCHI, NNU> out;
     out.pack(NCHI == 1 ? w & 0xFFFFFFu : r2, w & 0xFFFFu, nu);
     if (active) {
@@ -2268,18 +2263,20 @@ template <int NCHI, int NNU>
 __global__ void k_load_encode(const uint32_t* key_sorted, const uint32_t* idx_sorted, const uint16_t* chi_tmp,
                               const float* v_tmp, int64_t n, void* codes_out, int64_t cap,
                               const float* vc, const float* vinv, int64_t nc3, const float* edges,
-                              const int16_t* bucket, int nbucket, int vhalf, void* pid_out, int pid_bytes) {
+                              int vhalf, void* pid_out, int pid_bytes) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n) return;
   const int64_t src = idx_sorted[j];
   const int64_t c = key_sorted[j];
   const float inv = vinv[c];
   int ch[3], nu[3];
+  float u[3];
+#pragma unroll
   for (int d = 0; d < 3; ++d) {
     ch[d] = (int)chi_tmp[d * n + src];
-    const float u = (v_tmp[d * n + src] - vc[d * nc3 + c]) * inv;
-    nu[d] = encode_nu<true>(u, edges, bucket, nbucket, vhalf);
+    u[d] = (v_tmp[d * n + src] - vc[d * nc3 + c]) * inv;
   }
+  encode_nu3<NNU>(u, edges, vhalf, nu);
   Codes<NCHI, NNU> w;
   w.set(ch, nu);
   w.store(codes_out, cap, j);
@@ -2553,8 +2550,6 @@ static MoveArgs move_args(const Sim& s, int cur, float kfac, float dfac, bool de
   a.df = dfac;
   a.tdec = s.tdec;
   a.tedge = s.tedge;
-  a.tbucket = s.tbucket;
-  a.nbucket = s.nbucket;
   a.vhalf = (s.vm - 1) / 2;
   a.mig = s.mig;
   a.mom = s.mom;
@@ -2831,7 +2826,7 @@ void launch_load(Sim& s, const double* dx, const float* /*unused*/, int64_t n, h
 #define CUBE_ENC(X, V)                                                                                       \
   k_load_encode<X, V><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(ks, is, chi_tmp, v_tmp, n, s.codes[nxt],  \
                                                                    s.capacity, s.vc[nxt], s.vinv, \
-                                                                   s.nc3, s.tedge, s.tbucket, s.nbucket, (s.vm - 1) / 2, \
+                                                                   s.nc3, s.tedge, (s.vm - 1) / 2, \
                                                                    s.pid[nxt], s.pid_bytes)
   if (n > 0) {
     CUBE_XV_DISPATCH(s.nchi, s.nnu, CUBE_ENC);
