@@ -233,6 +233,17 @@ __device__ __forceinline__ unsigned long long wave_scan_u64(unsigned long long v
   return ((unsigned long long)hi << 32) | lo;
 }
 
+// the same for values whose sum is below 2^32
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);  // row_shr:1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);  // row_shr:2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);  // row_shr:4
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);  // row_shr:8
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast:31
+  return v;
+}
+
 __device__ __forceinline__ unsigned long long read_lane_u64(unsigned long long v, int lane) {
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane);
@@ -308,9 +319,12 @@ constexpr int MANY = 12;  // lanes on one corner cell from which their weights a
 // reads. A particle of the ring that reaches nothing is skipped by one comparison of its corner.
 //
 // Bound by vector issue where particles are spread (116 instructions per 64 particles of the column) and by
-// LDS adds to one address where they cluster. With 512^3 particles on as many cells 1075 -> 749 us early
-// and 1370 -> 993 clustered against columns with a tested corner each and 4 layers a chunk; 256^3 on
-// 512^3 cells 412 -> 370.
+// LDS adds to one address where they cluster. With 512^3 particles on as many cells 1075 -> 685 us early
+// and 1370 -> 986 clustered against columns with a tested corner each and 4 layers a chunk; 256^3 on
+// 512^3 cells 412 -> 342. Where cells hold few particles the work per layer counts: the first wavefront alone
+// reads and scans the layer's counts, and a thread converts the same column of fine cells in every plane
+// (with all wavefronts scanning and the converted cells numbered anew 128^3 on 256^3 65 us, now 49; 96^3
+// on 192^3 39 and 29; 256^3 on 512^3 375 and 342).
 template <int DTX>
 struct DepCfg {
   static constexpr int DF = 4 * DTX;
@@ -362,10 +376,9 @@ __device__ __forceinline__ void deposit_column(const DepArgs& a, const unsigned 
     if (m > 2047u) atomicMax(&smax, m);
   }
   __syncthreads();
-  const bool narrow = NCHI == 1 && smax <= 2047u;
-  // the layer's source cells in the lanes of every wavefront: cells 0 .. 63 and 64 .. DRC - 1
-  uint32_t inc[2], tot;
-  uint64_t rel[2];
+  const bool narrow = NCHI == 1 && (uint32_t)__builtin_amdgcn_readfirstlane((int)smax) <= 2047u;
+  // the layer's source cells, in the lanes of the first wavefront: cells 0 .. 63 and 64 .. DRC - 1
+  __shared__ uint32_t layer[2];  // particles of the layer, and whether lanes will share cells
   uint32_t cnt_n[2];
   uint64_t off_n[2];
   auto request = [&](int sz) {
@@ -383,32 +396,40 @@ __device__ __forceinline__ void deposit_column(const DepArgs& a, const unsigned 
       }
     }
   };
-  request(cz0 - 1);
+  // this thread's column of fine cells, in a bordered plane and in a plane of the mesh
+  const int mine = ((int)threadIdx.x / DF + 1) * PX + (int)threadIdx.x % DF + 1;
+  const uint32_t out = (uint32_t)(4 * cy0 + (int)threadIdx.x / DF) * (uint32_t)a.pitch_f + (uint32_t)(4 * cx0 + (int)threadIdx.x % DF);
+  if (wave == 0) request(cz0 - 1);
   uint32_t* const rho32 = reinterpret_cast<uint32_t*>(rho);
   int first = ((4 * (cz0 - 1) - 1) % NSLOT + NSLOT) % NSLOT;  // slot of plane 4 sz - 1
   for (int sz = cz0 - 1; sz <= cz1; ++sz, first = first + 4 >= NSLOT ? first + 4 - NSLOT : first + 4) {
-    inc[0] = (uint32_t)wave_scan_u64(cnt_n[0]);
-    rel[0] = off_n[0] - (inc[0] - cnt_n[0]);
-    tot = (uint32_t)__builtin_amdgcn_readlane((int)inc[0], 63);
-    if constexpr (DRC > 64) {
-      inc[1] = tot + (uint32_t)wave_scan_u64(cnt_n[1]);
-      rel[1] = off_n[1] - (inc[1] - cnt_n[1]);
-      tot = (uint32_t)__builtin_amdgcn_readlane((int)inc[1], 63);
-    }
     if (wave == 0) {
+      uint32_t inc[2];
+      inc[0] = wave_scan_u32(cnt_n[0]);
+      uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)inc[0], 63);
+      if constexpr (DRC > 64) {
+        inc[1] = n + wave_scan_u32(cnt_n[1]);
+        n = (uint32_t)__builtin_amdgcn_readlane((int)inc[1], 63);
+      }
       cbeg[lane] = inc[0] - cnt_n[0];
-      crel[lane] = rel[0];
+      crel[lane] = off_n[0] - (inc[0] - cnt_n[0]);
       if (DRC > 64 && lane + 64 < DRC) {
         cbeg[lane + 64] = inc[1] - cnt_n[1];
-        crel[lane + 64] = rel[1];
+        crel[lane + 64] = off_n[1] - (inc[1] - cnt_n[1]);
       }
-      if (lane == 0) cbeg[DRC] = tot;
+      // lanes share a cell where it holds a good part of the layer's particles
+      bool crowd = __ballot((uint64_t)cnt_n[0] * 64u >= (uint64_t)MANY * n) != 0ull;
+      if constexpr (DRC > 64) crowd |= __ballot((uint64_t)cnt_n[1] * 64u >= (uint64_t)MANY * n) != 0ull;
+      if (lane == 0) {
+        cbeg[DRC] = n;
+        layer[0] = n;
+        layer[1] = crowd ? 1u : 0u;
+      }
+      if (sz < cz1) request(sz + 1);
     }
     __syncthreads();
-    // lanes share a cell where it holds a good part of the layer's particles
-    bool crowded = __ballot((uint64_t)cnt_n[0] * 64u >= (uint64_t)MANY * tot) != 0ull;
-    if constexpr (DRC > 64) crowded |= __ballot((uint64_t)cnt_n[1] * 64u >= (uint64_t)MANY * tot) != 0ull;
-    if (sz < cz1) request(sz + 1);
+    const uint32_t tot = (uint32_t)__builtin_amdgcn_readfirstlane((int)layer[0]);
+    const bool crowded = __builtin_amdgcn_readfirstlane((int)layer[1]) != 0;
     const int zmin = pz0 - 1 - 4 * sz, zmax = pz1 - 1 - 4 * sz;  // corner planes that reach the owned ones
     auto deposit_layer = [&](auto* acc, auto crowd) {
       using A = typename std::remove_pointer<decltype(acc)>::type;
@@ -516,12 +537,13 @@ __device__ __forceinline__ void deposit_column(const DepArgs& a, const unsigned 
     __syncthreads();
     // planes 4 sz - 1 .. 4 sz + 2 are complete: write the owned ones, clear all (what the borders
     // collect is never read)
-    for (int i = threadIdx.x; i < 4 * DF * DF; i += BLK) {
-      const int pl = i / (DF * DF), e = i % (DF * DF), pz = 4 * sz - 1 + pl;
-      const int y = e / DF, x = e - y * DF;
+    static_assert(BLK == DF * DF, "a thread converts one column of fine cells");
+#pragma unroll
+    for (int pl = 0; pl < 4; ++pl) {
+      const int pz = 4 * sz - 1 + pl;
       int sl = first + pl;
       sl = sl >= NSLOT ? sl - NSLOT : sl;
-      const int idx = sl * PLANE + (y + 1) * PX + x + 1;
+      const int idx = sl * PLANE + mine;
       double r;
       if (narrow) {
         r = (double)rho32[idx];
@@ -530,8 +552,7 @@ __device__ __forceinline__ void deposit_column(const DepArgs& a, const unsigned 
         r = (double)rho[idx];
         rho[idx] = 0ull;
       }
-      if (pz >= pz0 && pz < pz1)
-        a.mesh[((int64_t)pz * a.nm + (4 * cy0 + y)) * a.pitch_f + (4 * cx0 + x)] = (float)(r * a.inv_mean - 1.0);
+      if (pz >= pz0 && pz < pz1) (a.mesh + (int64_t)pz * a.nm * a.pitch_f)[out] = (float)(r * a.inv_mean - 1.0);
     }
     __syncthreads();
   }
