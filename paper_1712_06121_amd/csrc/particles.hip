@@ -1933,12 +1933,12 @@ struct LinkArgs {
 };
 
 // the per-cell dispersion term n dev 2^20 stays below 2^54, so that the int64 sums of the 256 cells
-// of a link block cannot overflow; the sum over the blocks is exact in 128 bits (k_scan_blocks)
+// of a link block cannot overflow; the sum over the blocks is exact in 128 bits (k_scan_blocks, k_finalize)
 constexpr double kDevTermLimit = 18014398509481984.0;  // 2^54
 
 // Bound by memory latency, then by its 27 words read and written per cell: the 27 counts and the
 // four moments of a cell are requested together (with one load waiting for the store before it, a
-// 16^3 box took 15 us). Cell indices fit 32 bits (nc <= 512), plane bases are uniform.
+// 16^3 box took 15 us, now 6; 128^3 cells 139 -> 145 with the moment table, 630 MB). Cell indices fit 32 bits (nc <= 512), plane bases are uniform.
 __device__ __forceinline__ void link_block(const LinkArgs& a, const unsigned blk) {
   __shared__ unsigned long long sn[LINK_BLK / 64], sq[LINK_BLK / 64];
   if (workgroup_step_failed(a.flags)) return;
@@ -2309,33 +2309,33 @@ __global__ void k_load_encode(const uint32_t* key_sorted, const uint32_t* idx_so
 // Between the packed words and the checkpoint's planes (chi: 3 planes of n codes, nu: 3 planes of n)
 template <int NCHI, int NNU>
 __global__ __launch_bounds__(256) void k_unpack_codes(const void* codes, int64_t cap, int64_t n, void* chi, void* nu) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  Codes<NCHI, NNU> w;
-  w.load(codes, cap, j);
-  int ch[3], nv[3];
-  w.chi(ch);
-  w.nu(nv);
+  for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < n; j += (int64_t)gridDim.x * 256) {
+    Codes<NCHI, NNU> w;
+    w.load(codes, cap, j);
+    int ch[3], nv[3];
+    w.chi(ch);
+    w.nu(nv);
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    static_cast<chi_t<NCHI>*>(chi)[d * n + j] = (chi_t<NCHI>)ch[d];
-    static_cast<nu_t<NNU>*>(nu)[d * n + j] = (nu_t<NNU>)nv[d];
+    for (int d = 0; d < 3; ++d) {
+      static_cast<chi_t<NCHI>*>(chi)[d * n + j] = (chi_t<NCHI>)ch[d];
+      static_cast<nu_t<NNU>*>(nu)[d * n + j] = (nu_t<NNU>)nv[d];
+    }
   }
 }
 
 template <int NCHI, int NNU>
 __global__ __launch_bounds__(256) void k_pack_codes(const void* chi, const void* nu, int64_t n, void* codes, int64_t cap) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  int ch[3], nv[3];
+  for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < n; j += (int64_t)gridDim.x * 256) {
+    int ch[3], nv[3];
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    ch[d] = (int)static_cast<const chi_t<NCHI>*>(chi)[d * n + j];
-    nv[d] = (int)static_cast<const nu_t<NNU>*>(nu)[d * n + j];
+    for (int d = 0; d < 3; ++d) {
+      ch[d] = (int)static_cast<const chi_t<NCHI>*>(chi)[d * n + j];
+      nv[d] = (int)static_cast<const nu_t<NNU>*>(nu)[d * n + j];
+    }
+    Codes<NCHI, NNU> w;
+    w.set(ch, nv);
+    w.store(codes, cap, j);
   }
-  Codes<NCHI, NNU> w;
-  w.set(ch, nv);
-  w.store(codes, cap, j);
 }
 
 // IDs 0 .. n-1 in storage order
@@ -2426,7 +2426,7 @@ __global__ __launch_bounds__(256) void k_ic_table(ICTable c, float* __restrict__
 
 // side of the deposit's columns in coarse cells: 8, where the ring is 36 cells to 64 and a workgroup of 16
 // wavefronts shares its planes; 4 in boxes of at most 32 cells a side, which have too few columns of 8
-// to fill the chip (16^3 cells 27 -> 14 us; with 64^3 cells columns of 4 take 232 us, of 8 135)
+// to fill the chip (16^3 cells 27 -> 14 us; with 64^3 cells columns of 4 take 232 us, of 8 113)
 static int deposit_dtx(const Sim& s) { return s.nc <= 32 ? 4 : 8; }
 
 // the deposit's arguments for the state of parity cur, and its grid (columns x z chunks)
@@ -2870,12 +2870,15 @@ void staged_planes(const Sim& s, void** chi, void** nu) {
   *nu = chi_first ? w + (size_t)3 * s.n * s.nchi : w;
 }
 
+// workgroups of the two conversions, which go round the particles: a launch holds less than 2^32 threads
+static unsigned pack_blocks(int64_t n) { return (unsigned)std::min<int64_t>((n + 255) / 256, 65536); }
+
 void launch_unpack_codes(Sim& s, hipStream_t st) {
   if (s.n == 0) return;
   void *chi, *nu;
   staged_planes(s, &chi, &nu);
 #define CUBE_UNPACK(X, V) \
-  k_unpack_codes<X, V><<<(unsigned)((s.n + 255) / 256), 256, 0, st>>>(s.codes[s.cur], s.capacity, s.n, chi, nu)
+  k_unpack_codes<X, V><<<pack_blocks(s.n), 256, 0, st>>>(s.codes[s.cur], s.capacity, s.n, chi, nu)
   CUBE_XV_DISPATCH(s.nchi, s.nnu, CUBE_UNPACK);
 #undef CUBE_UNPACK
   CUBE_HIP(hipGetLastError());
@@ -2886,7 +2889,7 @@ void launch_pack_codes(Sim& s, hipStream_t st) {
   void *chi, *nu;
   staged_planes(s, &chi, &nu);
 #define CUBE_PACK(X, V) \
-  k_pack_codes<X, V><<<(unsigned)((s.n + 255) / 256), 256, 0, st>>>(chi, nu, s.n, s.codes[s.cur], s.capacity)
+  k_pack_codes<X, V><<<pack_blocks(s.n), 256, 0, st>>>(chi, nu, s.n, s.codes[s.cur], s.capacity)
   CUBE_XV_DISPATCH(s.nchi, s.nnu, CUBE_PACK);
 #undef CUBE_PACK
   CUBE_HIP(hipGetLastError());
