@@ -163,6 +163,13 @@ __device__ __forceinline__ bool workgroup_step_failed(const uint32_t* flags) {
   return failed != 0u;
 }
 
+// The deposit and the count pass of a phase enqueued behind a failed one find their state in the buffer
+// that the failed phase left as it was (never written, or a new count beside an old offset): they must not
+// follow it. flags[1], the failed phase's code, says so; it is written between phases only, so the
+// workgroups of a launch agree. (flags[0] may be raised by the launch itself, whose other tiles still
+// have to raise theirs: the most telling of the errors is the one reported.)
+__device__ __forceinline__ bool earlier_phase_failed(const uint32_t* flags) { return flags[1] != 0u; }
+
 // exclusive prefix of up to 256 uint32 values held one per thread; returns the total
 __device__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* out, int n, uint32_t* wsum) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -302,6 +309,7 @@ struct DepArgs {
   int nm, nc;
   int zc;  // coarse layers per z chunk
   double inv_mean;
+  const uint32_t* flags;
 };
 
 constexpr int NSLOT = 6;  // fine planes a coarse layer can touch
@@ -342,6 +350,7 @@ __device__ __forceinline__ void deposit_column(const DepArgs& a, const unsigned 
   __shared__ uint32_t cbeg[(DRC > 64 ? DRC : 64) + 1];
   __shared__ uint64_t crel[DRC > 64 ? DRC : 64];
   __shared__ int corner[DRC];  // word of fine cell (0, 0) of a source cell in a bordered plane
+  const bool failed = earlier_phase_failed(a.flags);  // requested first, tested before a code is read
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const unsigned ncol = (unsigned)(a.nc / DTX), cols = ncol * ncol;
@@ -376,6 +385,7 @@ __device__ __forceinline__ void deposit_column(const DepArgs& a, const unsigned 
     if (m > 2047u) atomicMax(&smax, m);
   }
   __syncthreads();
+  if (failed) return;
   const bool narrow = NCHI == 1 && (uint32_t)__builtin_amdgcn_readfirstlane((int)smax) <= 2047u;
   // the layer's source cells, in the lanes of the first wavefront: cells 0 .. 63 and 64 .. DRC - 1
   __shared__ uint32_t layer[2];  // particles of the layer, and whether lanes will share cells
@@ -1000,6 +1010,7 @@ __device__ __forceinline__ void count_tile(MoveArgs a, const unsigned lb) {
   __shared__ float4 cellv[TC];                      // mean velocity and decode scale of the own cells
   __shared__ float tdec_lds[NNU == 1 ? 255 : 1];
   __shared__ uint32_t top[2];
+  const bool failed = earlier_phase_failed(a.flags);  // requested first, tested with the counts
   const TileGeom g = tile_of((int)lb, a.nt);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1051,6 +1062,14 @@ __device__ __forceinline__ void count_tile(MoveArgs a, const unsigned lb) {
   for (int i = threadIdx.x; i < 2 * CSLOT; i += CNTH) reinterpret_cast<uint4*>(mom)[i] = make_uint4(0u, 0u, 0u, 0u);
   for (int i = threadIdx.x; i < TC * 27 / 4; i += CNTH) reinterpret_cast<uint4*>(left)[i] = make_uint4(0u, 0u, 0u, 0u);
   if (threadIdx.x < 2) top[threadIdx.x] = 0u;
+  if (failed) return;
+  if constexpr (MODE != 2) {
+    // no code is read and no record written past the end of storage, whatever the counts say
+    if (__ballot(beg + cnt > (uint64_t)a.cap)) {
+      if (threadIdx.x == 0) set_flag(a.flags, FLAG_COUNT);
+      return;
+    }
+  }
   // inclusive prefix of the counts over the own cells, in the lanes of every wavefront
   const uint32_t inc = (uint32_t)wave_scan_u64(cnt);
   const uint64_t rel = beg - (inc - cnt);  // storage index of a cell's particle i of the tile: rel + i
@@ -2449,6 +2468,7 @@ static DepArgs deposit_args(const Sim& s, int cur, dim3* grid) {
   a.zc = (s.nc + nchunk - 1) / nchunk;
   nchunk = (s.nc + a.zc - 1) / a.zc;
   a.inv_mean = (double)s.nm * (double)s.nm * (double)s.nm / ((double)s.n * ldexp(1.0, 3 * (8 * s.nchi - 1)));
+  a.flags = s.flags;
   *grid = dim3((unsigned)cols, (unsigned)nchunk);
   return a;
 }
