@@ -96,7 +96,9 @@ const char* cube_last_error(const cube_sim* sim);
 
 /* Zel'dovich initial conditions at a_init (Sec. 2.3.2, Fig. ic): Philox white noise on the
  * np_side^3 lattice, FFT, BBKS amplitude, spectral displacement with Nyquist planes removed,
- * then the two particle passes (count, then encode in cell order). Resets the schedule. */
+ * then the two particle passes (count, then encode in cell order). Resets the schedule. After an
+ * error of these passes (CUBE_E_CFL: a displacement of more than a coarse cell, CUBE_E_OVERFLOW) the
+ * simulation holds no particles. */
 int cube_init_ic(cube_sim* sim);
 /* Refined initial conditions, for the PM-error reference of Sec. 3 (the same initial conditions
  * with more particles and cells): with parent_np > 0 every later cube_init_ic and
@@ -111,7 +113,8 @@ int cube_set_ic_parent(cube_sim* sim, int32_t parent_np);
 /* Replace the particles by n host particles: x (n,3) positions in fine cells, v (n,3) momenta,
  * both FP64 row-major. Positions are encoded with Eq. (chi) in FP64, velocities rounded to
  * FP32 and encoded with Eq. (nu) against the statistics of their cell; storage order is the
- * input order, stably sorted by cell. Resets the schedule. Errors: CUBE_E_CAPACITY. */
+ * input order, stably sorted by cell. Resets the schedule. Errors: CUBE_E_CAPACITY,
+ * CUBE_E_NONFINITE, CUBE_E_OVERFLOW; the particles that were there stay then. */
 int cube_load_particles(cube_sim* sim, const double* x, const double* v, int64_t n);
 
 /* Advance k leapfrog steps (Fig. code): before the first step the initial half drift; each step

@@ -587,16 +587,26 @@ int cube_init_ic(cube_sim* sim) {
     float* wk = nullptr;
     cube::release_records(s);  // the displacement fields take their room
     cube::ic_fields(s, psi, &wk, temps, true);
-    s.n = (int64_t)s.np * s.np * s.np;
-    if (s.n > s.capacity) throw Error{CUBE_E_CAPACITY, "np_side^3 exceeds the capacity"};
+    // a displacement field may lie in the current state's codes: from here on there are no particles until the
+    // new ones have passed the flags (a refused move leaves counts, offsets or both unwritten)
+    s.have_particles = false;
+    s.n = 0;
+    const int64_t n = (int64_t)s.np * s.np * s.np;
+    if (n > s.capacity) throw Error{CUBE_E_CAPACITY, "np_side^3 exceeds the capacity"};
+    s.n = n;
     const double a = s.p.a_init;
     const float vfac = (float)(a * a * s.cosmo.E(a) * s.cosmo.f(a));
     cube::launch_move(s, 2, 0.0f, 0.0f, psi, vfac, s.stream, nullptr);
     CUBE_HIP(hipStreamSynchronize(s.stream));
     for (void* t : temps) s.dfree(t);
+    try {
+      cube::check_flags(s);
+    } catch (const Error&) {
+      s.n = 0;
+      throw;
+    }
     s.have_particles = true;
     cube::reset_schedule(s);
-    cube::check_flags(s);
   });
   return CUBE_OK;
 }
@@ -642,12 +652,21 @@ int cube_load_particles(cube_sim* sim, const double* x, const double* v, int64_t
       CUBE_HIP(hipMemcpyAsync(d, x, sizeof(double) * 3 * n, hipMemcpyHostToDevice, s.stream));
       CUBE_HIP(hipMemcpyAsync(d + 3 * n, v, sizeof(double) * 3 * n, hipMemcpyHostToDevice, s.stream));
     }
+    const int cur0 = s.cur;
+    const int64_t n0 = s.n;
     s.n = n;
-    cube::launch_load(s, d, nullptr, n, s.stream);
-    s.dfree(d);
+    try {
+      cube::launch_load(s, d, nullptr, n, s.stream);
+      s.dfree(d);
+      cube::check_flags(s);
+    } catch (const Error&) {
+      // not loaded: the load fills the other buffers, and the state that was there stays
+      s.cur = cur0;
+      s.n = n0;
+      throw;
+    }
     s.have_particles = true;
     cube::reset_schedule(s);
-    cube::check_flags(s);
   });
   return CUBE_OK;
 }

@@ -102,3 +102,49 @@ def test_batch_steps_behind_a_failed_half_drift(lib, cloud, code, mode):
         sim.load_particles(*cold_cloud(drift0, 5))
         sim.step(4)
         same(got, sim.get_state(), "the other box")
+
+
+def test_refused_initial_conditions_leave_no_particles(lib):
+    """Displacements of many coarse cells: the new counts and offsets were not written, so nothing may
+    take them for a state."""
+    cfg = dict(np_side=32, nm_side=64, box=50.0, omega_m=0.3, n_steps=10, spacing=1, seed=5)
+    with lib.Sim(**cfg) as sim:
+        sim.init_ic()
+        want = sim.get_state()
+    with lib.Sim(**dict(cfg, sigma8=500.0)) as sim:
+        for _ in range(2):
+            with pytest.raises(lib.CubeError) as e:
+                sim.init_ic()
+            assert e.value.code == -5 and sim.n == 0
+            for call in (lambda: sim.step(3), sim.get_state, sim.stage_deposit, lambda: sim.stage_move(0.0, 0.0)):
+                with pytest.raises(lib.CubeError) as e:
+                    call()
+                assert e.value.code == -8
+        sim.set_state(*(want[key] for key in KEYS))
+        same(sim.get_state(), want, "a state set afterwards")
+
+
+@pytest.mark.parametrize("bad,code", [(float("nan"), -7), (40000.0, -7)])
+def test_refused_particles_leave_the_ones_that_were_there(lib, bad, code):
+    x, v = cold_cloud(0.0, 9)
+    v[11, 1] = bad
+    with lib.Sim(**CFG) as sim:
+        with pytest.raises(lib.CubeError) as e:
+            sim.load_particles(x, v)
+        assert e.value.code == code
+        with pytest.raises(lib.CubeError) as e:
+            sim.step(1)
+        assert e.value.code == -8  # there were none
+        sim.load_particles(*cold_cloud(0.0, 5))
+        sim.step(1)
+        before = sim.get_state()
+        with pytest.raises(lib.CubeError) as e:
+            sim.load_particles(x[:5000], v[:5000])
+        assert e.value.code == code and sim.n == 20011 and sim.steps_done == 1
+        same(sim.get_state(), before, "after the refused load")
+        sim.step(3)
+        got = sim.get_state()
+    with lib.Sim(**CFG) as sim:
+        sim.load_particles(*cold_cloud(0.0, 5))
+        sim.step(4)
+        same(got, sim.get_state(), "the run goes on")
