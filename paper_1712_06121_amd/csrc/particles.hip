@@ -22,6 +22,7 @@
 
 
 #include "cube_internal.h"
+#include "launch_groups.h"
 
 namespace cube {
 namespace {
@@ -993,7 +994,7 @@ __device__ __forceinline__ int find_cell_in(const uint32_t* pre, int lo, int hi,
 // the latencies of the tile's set-up and flush; with step maxima, 96^3 on 128^3, 392 -> 28 us (an atomic
 // pair on one address per 64 particles before, one per tile now).
 // ---------------------------------------------------------------------------------------------
-constexpr int CNTH = 1024;       // threads per workgroup
+constexpr int CNTH = kCountThreads;  // threads per workgroup
 constexpr int CCOPY = 8;         // copies of an own cell's moment accumulators
 constexpr int CPX = F + 8;       // potential row in LDS: 24 floats
 constexpr int CPP = PH * CPX + 12;  // potential plane in LDS
@@ -2704,8 +2705,7 @@ StagedBoxes stage_boxes(EnsembleStep& es, const std::vector<A>& args, const std:
     t += b;
     first.push_back((uint32_t)t);
   }
-  // a dispatch holds fewer than 2^32 work-items
-  if (t * (uint64_t)threads >= (1ull << 32)) throw Error{CUBE_E_INVALID, "ensemble too large for one launch per stage"};
+  if (!fits_dispatch(t, (uint64_t)threads)) throw Error{CUBE_E_INVALID, "ensemble too large for one launch per stage"};
   return StagedBoxes{es.put(args), es.put(first), (int)args.size(), (unsigned)t};
 }
 
@@ -2772,9 +2772,19 @@ void ensemble_move(EnsembleStep& es, const std::vector<Sim*>& boxes) {
           per.push_back((uint32_t)(nt * nt * nt));
         }
         if (args.empty()) continue;
-        const StagedBoxes g = stage_boxes(es, args, per, tile >= 2 ? PLACE_BLK : (tile ? 1024 : 512));
-        es.launches.push_back([e, g, nchi, nnu, tile, scatter](hipStream_t st) {
-          const BoxTable<MoveArgs> t = table_of<MoveArgs>(e, g);
+        // The count pass's workgroups are twice as wide as those of the per-corner scatter, which bounds an
+        // ensemble at 2^23 tiles: from 2^22 on it takes two launches
+        const int threads = scatter ? (tile >= 2 ? PLACE_BLK : (tile ? 1024 : 512)) : CNTH;
+        uint64_t tiles = 0;
+        for (uint32_t b : per) tiles += b;
+        if (!scatter && !fits_dispatch(tiles, 512)) throw Error{CUBE_E_INVALID, "ensemble too large for one launch per stage"};
+        const std::vector<size_t> runs = scatter ? std::vector<size_t>{0, per.size()} : box_runs(per, (uint64_t)threads);
+        for (size_t i = 0; i + 1 < runs.size(); ++i) {
+          const size_t b0 = runs[i], b1 = runs[i + 1];
+          const StagedBoxes g = stage_boxes(es, std::vector<MoveArgs>(args.begin() + b0, args.begin() + b1),
+                                            std::vector<uint32_t>(per.begin() + b0, per.begin() + b1), threads);
+          es.launches.push_back([e, g, nchi, nnu, tile, scatter](hipStream_t st) {
+            const BoxTable<MoveArgs> t = table_of<MoveArgs>(e, g);
 #define CUBE_PASS(X, V)                                                                                 \
   do {                                                                                                  \
     if (tile == 3) k_place_boxes<X, V, true><<<g.blocks, PLACE_BLK, 0, st>>>(t);                         \
@@ -2783,10 +2793,11 @@ void ensemble_move(EnsembleStep& es, const std::vector<Sim*>& boxes) {
     else if (scatter) k_move_scatter_boxes<X, V, 0, 512><<<g.blocks, 512, 0, st>>>(t);            \
     else k_count_boxes<X, V><<<g.blocks, CNTH, 0, st>>>(t);                                              \
   } while (0)
-          CUBE_XV_DISPATCH(nchi, nnu, CUBE_PASS);
+            CUBE_XV_DISPATCH(nchi, nnu, CUBE_PASS);
 #undef CUBE_PASS
-          CUBE_HIP(hipGetLastError());
-        });
+            CUBE_HIP(hipGetLastError());
+          });
+        }
       }
   };
   pass(false);
