@@ -503,15 +503,18 @@ __device__ __forceinline__ void deposit_column(const DepArgs& a, const unsigned 
         // summed over the wavefront first
         unsigned long long todo = __ballot(reach);
         const int key = sl * PLANE + at;
+        const int key_up = up * PLANE + at;
         while (decltype(crowd)::value && todo) {
-          const int lead = __builtin_amdgcn_readlane(key, __ffsll((long long)todo) - 1);
+          // the crowd's two words, from its first lane while every lane is active
+          const int first_lane = __ffsll((long long)todo) - 1;
+          const int lead = __builtin_amdgcn_readlane(key, first_lane), lead_up = __builtin_amdgcn_readlane(key_up, first_lane);
           const unsigned long long same = __ballot(key == lead) & todo;
           if (__popcll(same) < MANY) break;
           const bool in = (same >> lane) & 1ull;
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
             const W t = wave_total(in ? weight(j) : (W)0);
-            if (lane == 63 - j) atomicAdd(acc + __builtin_amdgcn_readlane(word(j), __ffsll((long long)same) - 1), (A)t);
+            if (lane == 63 - j) atomicAdd(acc + ((j >> 2) ? lead_up : lead) + ((j >> 1) & 1) * PX + (j & 1), (A)t);
           }
           todo &= ~same;
         }
