@@ -124,6 +124,12 @@ int cube_load_particles(cube_sim* sim, const double* x, const double* v, int64_t
  * step whose move raises a flag is not applied, and neither is any later one: the call then
  * returns the error with the state, cube_steps_done and cube_scale_factor those before the
  * failing step (or before the initial half drift), and the error text names that step.
+ * For the length of the call a simulation may hold 16 bytes per particle of capacity (20 with
+ * x_bytes 2) beyond its own device memory: the records of moved particles that the count pass leaves
+ * for the scatter. Where they do not fit (the allocator returns NULL, or above 1 GB less than as much
+ * again would stay free), from a capacity of 2^31 on, and where hipMalloc would cost more than they
+ * save, the scatter recomputes the move, with the same result. cube_batch_step, cube_stage_move and
+ * cube_autotune do the same.
  * Errors: CUBE_E_CFL, CUBE_E_NONFINITE, CUBE_E_OVERFLOW (a velocity of 2^15 fine cells x H0 or
  * more, or a coarse cell whose n x 3-D velocity variance reaches 2^34), CUBE_E_STATE. */
 int cube_step(cube_sim* sim, int32_t k);
@@ -155,7 +161,7 @@ int cube_debug_inject_flag(cube_sim* sim, int32_t step, uint32_t flag);
  * each chunk waiting (polling an LDS word) until the previous one is ranked; after `polls` polls
  * (default 2^22, far beyond any legitimate wait) a chunk stops waiting and raises the count error
  * (8), so the step fails with CUBE_E_STATE and is not applied. A small value forces that path.
- * Steps normally place the records their count pass wrote (where there is device memory for them);
+ * Steps normally place the records their count pass wrote (see cube_step);
  * a limit other than the default makes them recompute the move in the scatter of move_variant, with
  * the same results. Errors: CUBE_E_INVALID (polls 0). */
 int cube_debug_set_turn_limit(cube_sim* sim, uint32_t polls);
@@ -298,7 +304,7 @@ int cube_get_tables(cube_sim* sim, float* decode, float* edges);
  * for j = 0 .. n_steps-1. kick/drift must have n_steps entries. */
 int cube_get_schedule(const cube_sim* sim, double* drift0, double* kick, double* drift);
 
-/* Device memory held by the simulation, in bytes. */
+/* Device memory held by the simulation, in bytes (between calls: without the records of cube_step). */
 int64_t cube_device_bytes(const cube_sim* sim);
 
 /* Average time per step of each kernel of the last cube_step call, measured with HIP events on
@@ -313,8 +319,8 @@ int cube_get_timings(const cube_sim* sim, double* ms9);
  * Some stages have equivalent kernel variants that give bit-identical results: the layout of the
  * work, never the arithmetic, differs. */
 typedef struct {
-  int32_t move_variant;    /* whether the scatter of a step that recomputes the move (where the
-                              records of moved particles do not fit the device) uses the gradient
+  int32_t move_variant;    /* whether the scatter of a step that recomputes the move (without the
+                              records of moved particles, see cube_step) uses the gradient
                               tile (the 4-point gradient of the whole tile precomputed in LDS,
                               1024-thread workgroups) instead of the gradient per CIC corner
                               (512-thread workgroups): 1 and 2 yes, 0 (default) and 3 no; -1: yes
@@ -401,7 +407,9 @@ int cube_batch_step(cube_batch* b, int32_t k);
 typedef struct cube_server cube_server;
 
 /* Device bytes that cube_create followed by cube_init_ic allocates for these parameters at most
- * (allocator rounding not included); negative (CUBE_E_INVALID) for malformed parameters. */
+ * (allocator rounding not included), and that the job of a server holds at most; negative
+ * (CUBE_E_INVALID) for malformed parameters. What a step call may hold beyond it, and only until it
+ * returns, stands at cube_step. */
 int64_t cube_footprint(const cube_params* params);
 
 /* mem_budget_bytes: admission limit on the sum of the footprints of admitted, not yet released

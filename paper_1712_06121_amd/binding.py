@@ -622,7 +622,8 @@ def counts_from_u8(rho1, overflow) -> np.ndarray:
 
 
 def footprint(**cfg) -> int:
-    """Device bytes a simulation of these parameters allocates at most (``cube_footprint``)."""
+    """Device bytes that creating a simulation of these parameters and its initial conditions allocate
+    at most (``cube_footprint``); a step call may hold more until it returns (``cube_step``)."""
     lib = load_library()
     fp = lib.cube_footprint(byref(make_params(**cfg)))
     if fp < 0:

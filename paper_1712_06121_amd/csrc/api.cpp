@@ -17,22 +17,15 @@ namespace cube {
 void* Sim::dmalloc(size_t bytes) {
   void* p = nullptr;
   if (bytes == 0) bytes = 256;
-  auto try_alloc = [&]() {
-    if (has_alloc) {
-      p = alloc.alloc(bytes, alloc.user);
-    } else if (hipMalloc(&p, bytes) != hipSuccess) {
+  if (has_alloc) {
+    p = alloc.alloc(bytes, alloc.user);
+    if (!p) throw Error{CUBE_E_NOMEM, "device allocator returned NULL for " + std::to_string(bytes) + " bytes"};
+  } else {
+    if (hipMalloc(&p, bytes) != hipSuccess) {
       (void)hipGetLastError();
-      p = nullptr;
+      throw Error{CUBE_E_NOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed"};
     }
-  };
-  try_alloc();
-  if (!p && rec) {  // the records only save time: they make room for what is needed
-    release_records(*this);
-    try_alloc();
   }
-  if (!p)
-    throw Error{CUBE_E_NOMEM, (has_alloc ? "device allocator returned NULL for " : "hipMalloc failed for ") +
-                                  std::to_string(bytes) + " bytes"};
   dev_bytes += (int64_t)bytes;
   owned.push_back(p);
   sizes.push_back(bytes);
@@ -55,40 +48,89 @@ void Sim::dfree(void* p) {
 
 // helpers shared with batch.cpp (declared in cube_internal.h)
 
-// The records take room that the simulation could do without, so they are allocated only where as
-// much again stays free on the device (2048^3 particles recompute the move instead), or, for jobs
-// of a server, whose admission counts footprints, within the job's own footprint (its
-// initial-condition fields are gone by then). Indices of places are 32-bit: below 2^31 particles.
-void ensure_records(Sim& s) {
-  if (s.rec || s.capacity >= ((int64_t)1 << 31)) return;
-  const size_t need = (size_t)s.capacity * (s.nchi == 1 ? 16 : 20);
-  if (need == 0) return;
-  if (s.rec_in_footprint) {
-    if (s.dev_bytes + (int64_t)need > footprint_bytes(s.p)) return;
-  } else {
+// Bytes of a simulation's records, 0 where it has none. Indices of places are 32-bit: below 2^31 particles.
+static size_t record_bytes(const Sim& s) {
+  if (s.capacity >= ((int64_t)1 << 31) || s.turn_limit != kTurnLimit) return 0;
+  return ((size_t)s.capacity * (s.nchi == 1 ? 16 : 20) + 255) & ~(size_t)255;
+}
+
+// The records are held for the length of a call, so that between calls a simulation takes what it took
+// at its creation, and the caller, or another simulation, finds the device as free as without them.
+// Within the call they take memory only where as much again stays free (looked up above 1 GB: 2048^3
+// particles recompute the move).
+StepRecords::StepRecords(const std::vector<Sim*>& boxes, int64_t steps, hipStream_t also) : also_(also) {
+  size_t need = 0;
+  double particles = 0.0;
+  for (Sim* s : boxes) {
+    const size_t b = s->rec ? 0 : record_bytes(*s);
+    if (b == 0) continue;
+    boxes_.push_back(s);
+    need += b;
+    particles += (double)s->n;
+  }
+  if (steps < 1) boxes_.clear();
+  if (boxes_.empty()) return;
+  Sim& owner = *boxes_[0];
+  // They save 8 us a step (32^3 particles: the smallest boxes are bound by latency) and at least 8 ps a
+  // particle (512^3 with the gradient tile; 12 ps without at 256^3, 25 where cells hold few). hipMalloc and
+  // hipFree add 55 to 125 us to a call up to 64 MB, 430 at 256 MB and 800 at 17 GB; a caller's allocator is
+  // taken to keep its memory, as PyTorch's does (2 to 8 us).
+  const double saves = (double)steps * (8e-6 + 8e-12 * particles);
+  const double costs = owner.has_alloc ? 5e-6 : need <= ((size_t)64 << 20) ? 110e-6 : need <= ((size_t)1 << 30) ? 430e-6 : 800e-6;
+  if (saves < costs) {
+    boxes_.clear();
+    return;
+  }
+  if (need > ((size_t)1 << 30)) {
     size_t avail = 0, total = 0;
     if (hipMemGetInfo(&avail, &total) != hipSuccess) {
       (void)hipGetLastError();
+      avail = 0;
+    }
+    if (avail / 2 < need) {
+      boxes_.clear();
       return;
     }
-    if (avail / 2 < need) return;
   }
+  try {
+    block_ = owner.dmalloc(need);
+  } catch (const Error& e) {
+    boxes_.clear();
+    if (e.code != CUBE_E_NOMEM) throw;
+    return;
+  }
+  char* at = static_cast<char*>(block_);
+  for (Sim* s : boxes_) {
+    s->rec = at;
+    at += record_bytes(*s);
+  }
+}
+
+StepRecords::~StepRecords() {
+  if (!block_) return;
+  if (!idle_) {
+    for (Sim* s : boxes_) (void)hipStreamSynchronize(s->stream);
+    if (also_) (void)hipStreamSynchronize(also_);
+  }
+  for (Sim* s : boxes_) s->rec = nullptr;
+  boxes_[0]->dfree(block_);
+}
+
+void job_records(Sim& s) {
+  const size_t need = record_bytes(s);
+  if (s.rec || need == 0 || s.dev_bytes + (int64_t)need > footprint_bytes(s.p)) return;
   try {
     s.rec = static_cast<char*>(s.dmalloc(need));
   } catch (const Error& e) {
     if (e.code != CUBE_E_NOMEM) throw;
-    return;
   }
-  s.config_gen++;  // captured step graphs hold the other scatter
 }
 
-void release_records(Sim& s) {
+void release_job_records(Sim& s) {
   if (!s.rec) return;
-  if (s.stream) (void)hipStreamSynchronize(s.stream);
-  else (void)hipDeviceSynchronize();
+  (void)hipStreamSynchronize(s.stream);
   s.dfree(s.rec);
   s.rec = nullptr;
-  s.config_gen++;
 }
 
 void build_tables(Sim& s) {
@@ -186,7 +228,6 @@ void read_maxima(Sim& s, double* vmax, double* gmax) {
 
 int enqueue_adaptive(Sim& s, int k) {
   const double af = s.p.a_final;
-  if (k > 0) ensure_records(s);
   for (int i = 0; i < k; ++i) {
     if (!s.half_drift_done) {
       const double v0 = std::sqrt((double)launch_state_speed2(s, s.stream));
@@ -377,7 +418,6 @@ int enqueue_steps(Sim& s, int k) {
     for (double& t : s.timings) t = 0.0;
     s.timing_calls = 0;
   }
-  if (k > 0 && s.steps_done < s.p.n_steps) ensure_records(s);
   for (int i = 0; i < k; ++i) {
     if (s.steps_done >= s.p.n_steps) {
       rc = CUBE_DONE;
@@ -585,7 +625,6 @@ int cube_init_ic(cube_sim* sim) {
     std::vector<void*> temps;
     float* psi[3];
     float* wk = nullptr;
-    cube::release_records(s);  // the displacement fields take their room
     cube::ic_fields(s, psi, &wk, temps, true);
     // a displacement field may lie in the current state's codes: from here on there are no particles until the
     // new ones have passed the flags (a refused move leaves counts, offsets or both unwritten)
@@ -683,8 +722,10 @@ int cube_step(cube_sim* sim, int32_t k) {
   cube::Sim& s = sim->s;
   int rc = CUBE_OK;
   CUBE_GUARD(sim, {
+    cube::StepRecords rec({&s}, s.have_particles ? std::min(k, s.p.n_steps - s.steps_done) : 0);
     rc = cube::enqueue_steps(s, k);
     cube::check_flags(s);
+    rec.idle();
   });
   return rc;
 }
@@ -792,7 +833,7 @@ int cube_stage_move(cube_sim* sim, float kfac, float dfac) {
   CUBE_GUARD(sim, {
     cube::require_particles(sim->s);
     const int cur0 = sim->s.cur;
-    cube::ensure_records(sim->s);
+    cube::StepRecords rec({&sim->s}, cube::StepRecords::kWhereTheyFit);  // the kernels of long runs
     cube::launch_move(sim->s, 0, kfac, dfac, nullptr, 0.0f, sim->s.stream, nullptr);
     CUBE_HIP(hipStreamSynchronize(sim->s.stream));
     try {

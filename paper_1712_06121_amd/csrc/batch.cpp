@@ -30,7 +30,7 @@ struct cube_batch {
   std::unique_ptr<cube::EnsembleStep> table[2];  // mode 2: the launches and tables of each parity
   hipGraph_t graph[2] = {nullptr, nullptr};
   hipGraphExec_t exec[2] = {nullptr, nullptr};
-  std::vector<int> gens;  // each box's config_gen when the graphs were captured
+  std::vector<int> gens;  // each box's config_gen, and whether it held records, when the graphs were captured
   std::string last_error;
 };
 
@@ -123,10 +123,10 @@ void build_graph(cube_batch& b, int par) {
   CUBE_HIP(hipGraphInstantiate(&b.exec[par], b.graph[par], nullptr, nullptr, 0));
 }
 
-// drop captured graphs that a later change of a box (variants, particle IDs) has made stale
+// drop captured graphs that a later change of a box (variants, particle IDs, records) has made stale
 void check_graphs(cube_batch& b) {
   std::vector<int> now(b.boxes.size());
-  for (size_t i = 0; i < b.boxes.size(); ++i) now[i] = b.boxes[i]->s.config_gen;
+  for (size_t i = 0; i < b.boxes.size(); ++i) now[i] = 2 * b.boxes[i]->s.config_gen + (b.boxes[i]->s.rec ? 1 : 0);
   if (now != b.gens) {
     destroy_graphs(b);
     b.gens = now;
@@ -240,7 +240,7 @@ void autotune_sim(Sim& s) {
   // move: the count pass and the scatter from records have one kernel each; the recomputing scatter
   // (no room for the records) has two, per-corner gradient and gradient tile, timed by the events around
   // it with this step's factors
-  ensure_records(s);
+  StepRecords rec({&s}, StepRecords::kWhereTheyFit);
   const int j = std::min(s.steps_done, s.p.n_steps - 1);
   const float kf = (float)(-s.kicks[j] / 12.0), df = (float)s.drifts[j];
   float tc = 0.f, ts[2] = {0.f, 0.f};
@@ -477,8 +477,9 @@ int cube_batch_step(cube_batch* b, int32_t k) {
     for (cube::Sim* s : ss)
       if (s->steps_done != done || s->cur != ss[0]->cur)
         throw Error{CUBE_E_STATE, "boxes of a batch must be at the same step (step them with cube_batch_step only)"};
-    if (k > 0 && done < ss[0]->p.n_steps)
-      for (cube::Sim* s : ss) cube::ensure_records(*s);
+    // records for every call or for none, whatever k (the captured scatter depends on it): where one step
+    // pays for them
+    cube::StepRecords rec(ss, k > 0 && done < ss[0]->p.n_steps ? 1 : 0, b->main);
     // the initial half drift (no force) of every box, each on its own stream
     for (size_t i = 0; i < ss.size(); ++i) {
       cube::Sim& s = *ss[i];
@@ -489,9 +490,11 @@ int cube_batch_step(cube_batch* b, int32_t k) {
         s.half_drift_done = true;
       }
     }
+    std::vector<cube::StepWord> words(ss.size());
     for (size_t i = 0; i < ss.size(); ++i) {
       cube::Sim& s = *ss[i];
-      CUBE_HIP(hipMemcpyAsync(s.step_dev, &s.steps_done, sizeof(int), hipMemcpyHostToDevice, s.stream));
+      words[i] = cube::StepWord{s.steps_done, 0, (uint64_t)reinterpret_cast<uintptr_t>(cube::step_records(s))};
+      CUBE_HIP(hipMemcpyAsync(s.step_dev, &words[i], sizeof(words[i]), hipMemcpyHostToDevice, s.stream));
       CUBE_HIP(hipEventRecord(b->joins[i], s.stream));
       CUBE_HIP(hipStreamWaitEvent(b->main, b->joins[i], 0));
     }
@@ -524,6 +527,7 @@ int cube_batch_step(cube_batch* b, int32_t k) {
         CUBE_HIP(hipStreamWaitEvent(b->main, b->joins[bi], 0));
       }
     CUBE_HIP(hipStreamSynchronize(b->main));
+    rec.idle();
     // every box's flags are checked (a failed box goes back to the state before its failing step,
     // the others keep their steps); the first failure is reported
     std::string first;

@@ -175,7 +175,7 @@ struct Sim {
   std::vector<double> a_int, a_half, kicks, drifts;
   double drift0 = 0.0;
   float* sched_dev = nullptr;  // FP32 (-kick_j / 12, drift_j) per step (device)
-  int* step_dev = nullptr;     // step index read by graph-replayed move kernels (device)
+  int* step_dev = nullptr;     // step index and records read by graph-replayed move kernels (a StepWord, device)
   int steps_done = 0;
   bool half_drift_done = false;
   int move_variant = 0;     // move passes: -1 by particle density, 0 per-corner gradient, 1 gradient tile
@@ -203,10 +203,8 @@ struct Sim {
   uint32_t turn_limit = kTurnLimit;
 
   // Moved-particle records (16 bytes per particle of capacity, 20 with 2-byte positions) from the
-  // count pass to the scatter of a step; null when they are not used (ensure_records). Given back
-  // when another allocation needs the room.
+  // count pass to the scatter of a step; null outside the calls that use them (StepRecords, job_records)
   char* rec = nullptr;
-  bool rec_in_footprint = false;  // only while the simulation stays within its cube_footprint (server jobs)
 
   // profiling: per-kernel event pairs recorded on the simulation's stream
   bool profiling = false;
@@ -228,10 +226,35 @@ float gconst(const Sim& s);       // Green's constant -3/2 Omega_m / N^3
 void require_particles(const Sim& s);
 int enqueue_steps(Sim& s, int k);  // k steps on s.stream, no wait, flags unchecked; CUBE_DONE at a_final
 int64_t footprint_bytes(const cube_params& p);
-// The moved-particle records of the steps about to be enqueued (before a capture, since it may
-// allocate), and giving them back.
-void ensure_records(Sim& s);
-void release_records(Sim& s);
+// The moved-particle records of `boxes` (on one device, with one allocator) for the `steps` steps that a
+// call is about to enqueue, given back with the object; none where they do not fit or would not pay.
+class StepRecords {
+ public:
+  static constexpr int64_t kWhereTheyFit = (int64_t)1 << 40;  // steps: whatever the allocation costs
+  // also: a stream, beside the boxes' own, that the steps are enqueued on
+  StepRecords(const std::vector<Sim*>& boxes, int64_t steps, hipStream_t also = nullptr);
+  ~StepRecords();
+  void idle() { idle_ = true; }  // the steps have been waited for
+  StepRecords(const StepRecords&) = delete;
+  StepRecords& operator=(const StepRecords&) = delete;
+
+ private:
+  std::vector<Sim*> boxes_;  // those that hold records in block_
+  void* block_ = nullptr;
+  hipStream_t also_ = nullptr;
+  bool idle_ = false;
+};
+// The same for a server's job, whose steps go on from call to call: kept until given back, within the
+// job's footprint (its initial-condition fields are gone by then).
+void job_records(Sim& s);
+void release_job_records(Sim& s);
+// where the step kernels write records; null: the scatter recomputes the move
+inline char* step_records(const Sim& s) { return s.turn_limit == kTurnLimit ? s.rec : nullptr; }
+// what captured move kernels read on the device, uploaded once a call
+struct StepWord {
+  int32_t step, unused;
+  uint64_t rec;
+};
 
 // ---- launchers (implemented in the .hip files) ---------------------------------------------
 bool fft_size_supported(int n);

@@ -631,8 +631,8 @@ struct MoveArgs {
   uint32_t* amax;
   // moved particles (step and drift passes): when set, the count pass writes every particle's new
   // velocity, codes and displacement at its storage index, and k_place puts them in their new cells
+  // (device-side schedule: read from its step word)
   float4* rec;
-  uint32_t* rec2;
   // gradient-tile scatter: polls of the LDS turn word after which a chunk stops waiting for its
   // turn and raises the count error (the wait then ends whatever the other wavefronts do)
   uint32_t turn_limit;
@@ -677,6 +677,18 @@ __device__ __forceinline__ void resolve_factors(MoveArgs& a) {
   }
 }
 
+// The records of this launch. They are allocated for a call, so a captured launch reads where they lie.
+// The address space is named because the compiler cannot tell it of an address read from memory: with flat
+// loads k_place takes 174 us for 256^3 particles on as many cells, with global ones 149.
+typedef float rec4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(1))) rec4* Records;
+typedef __attribute__((address_space(1))) uint32_t* Records2;  // second plane, behind the first
+__device__ __forceinline__ Records records(const MoveArgs& a) {
+  const uint64_t r = a.kd ? *reinterpret_cast<const uint64_t*>(a.kstep + 2) : reinterpret_cast<uint64_t>(a.rec);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)r), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(r >> 32));
+  return (Records)(((uint64_t)hi << 32) | lo);
+}
+
 // rint(x s) as int64 for a power of two s and |x s| < 2^51: adding 1.5 * 2^52 rounds x s to the
 // nearest integer (ties to even, as rint does) in the low mantissa bits; the difference of the bit
 // patterns is that integer. x s is exact, so the fused multiply-add rounds once, as the sum would.
@@ -713,11 +725,11 @@ __device__ __forceinline__ void velocity_moments(const float* v, long long* q) {
 // (z y x digits of k + 1 in base 3). 16 bytes with 1-byte positions; 2-byte ones put the x and y codes
 // into a second plane of 4 bytes.
 template <int NCHI>
-__device__ __forceinline__ void store_record(const MoveArgs& a, int64_t p, const float* v, const int* chi, int dcode) {
+__device__ __forceinline__ void store_record(Records rec, int64_t cap, int64_t p, const float* v, const int* chi, int dcode) {
   const uint32_t w = NCHI == 1 ? (uint32_t)(chi[0] | (chi[1] << 8) | (chi[2] << 16) | (dcode << 24))
                                : (uint32_t)(chi[2] | (dcode << 16));
-  a.rec[p] = make_float4(v[0], v[1], v[2], __uint_as_float(w));
-  if constexpr (NCHI == 2) a.rec2[p] = (uint32_t)(chi[0] | (chi[1] << 16));
+  rec[p] = rec4{v[0], v[1], v[2], __uint_as_float(w)};
+  if constexpr (NCHI == 2) ((Records2)(rec + cap))[p] = (uint32_t)(chi[0] | (chi[1] << 16));
 }
 
 struct Moved {
@@ -1006,6 +1018,7 @@ constexpr int CSLOT = TC * CCOPY + RC;  // accumulators per moment: own cells' c
 template <int NCHI, int NNU, int MODE, bool MEAS>
 __device__ __forceinline__ void count_tile(MoveArgs a, const unsigned lb) {
   resolve_factors(a);
+  const Records rec = MODE != 2 ? records(a) : nullptr;
   constexpr int SH = 8 * NCHI - 1;
   constexpr int NW = CNTH / 64;
   __shared__ __align__(16) float ph[MODE == 0 ? PH * CPP : 4];
@@ -1251,7 +1264,7 @@ __device__ __forceinline__ void count_tile(MoveArgs a, const unsigned lb) {
     const int slot = stay ? s * CCOPY + (lane & (CCOPY - 1)) : TC * CCOPY + ring;
     if (active) {
       if constexpr (MODE != 2)
-        if (a.rec) store_record<NCHI>(a, pc, v, cq, dcode);
+        if (rec) store_record<NCHI>(rec, a.cap, pc, v, cq, dcode);
 #pragma unroll
       for (int d = 0; d < 4; ++d) atomicAdd(&mom[d * CSLOT + slot], (unsigned long long)q[d]);
       if (!stay) atomicAdd(&left[s * 27 + dcode], 1u);
@@ -1776,6 +1789,7 @@ __device__ __forceinline__ void place_tile(const MoveArgs& a, const unsigned lb)
   __shared__ float4 stat[RC];         // mean velocity and encode scale
   __shared__ float edges_lds[NNU == 1 ? 256 : 1];
   const uint32_t failed = __atomic_load_n(a.flags, __ATOMIC_RELAXED);
+  const Records rec = records(a);
   const TileGeom g = tile_of(lb, a.nt);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1857,20 +1871,20 @@ __device__ __forceinline__ void place_tile(const MoveArgs& a, const unsigned lb)
     // lanes past the end read the last particle
     p = rl + ((uint32_t)lane < left ? i : tot - 1u);
   };
-  float4 rn = make_float4(0.f, 0.f, 0.f, 0.f);
+  rec4 rn = {0.f, 0.f, 0.f, 0.f};
   uint32_t r2n = 0u, pn = 0u;
   uint64_t idn = 0u;
   int sn = 0;
   unsigned long long on = 0ull;
   auto request = [&]() {
-    rn = a.rec[pn];
-    if constexpr (NCHI == 2) r2n = a.rec2[pn];
+    rn = rec[pn];
+    if constexpr (NCHI == 2) r2n = ((Records2)(rec + a.cap))[pn];
     if constexpr (PID) idn = particle_id<0>(a, g, 0, (int64_t)pn, 0u);
   };
   // one chunk; FULL: every lane holds a particle
   auto chunk = [&](auto full, uint32_t c0) {
     constexpr bool FULL = decltype(full)::value;
-    const float4 rc = rn;
+    const rec4 rc = rn;
     const uint32_t r2 = r2n;
     const uint64_t id = idn;
     const int s = sn + WC * wave;
@@ -2568,7 +2582,7 @@ void launch_raise_flag(Sim& s, hipStream_t st, uint32_t f, bool dev_sched, int a
 // whether a step's scatter places the count pass's records (k_place) instead of recomputing the
 // move: when the record buffer is there; a poll limit other than the default asks for the ordered
 // scatter it belongs to
-static bool use_records(const Sim& s) { return s.rec && s.turn_limit == kTurnLimit; }
+static bool use_records(const Sim& s) { return step_records(s) != nullptr; }
 
 // the move passes' arguments from the state of parity cur to the other (no step maxima, no
 // initial-condition fields)
@@ -2605,10 +2619,7 @@ static MoveArgs move_args(const Sim& s, int cur, float kfac, float dfac, bool de
   a.pid_n = s.pid[nxt];
   a.pid_bytes = s.pid_bytes;
   a.amax = nullptr;
-  if (use_records(s)) {
-    a.rec = reinterpret_cast<float4*>(s.rec);
-    a.rec2 = reinterpret_cast<uint32_t*>(s.rec + sizeof(float4) * (size_t)s.capacity);
-  }
+  a.rec = reinterpret_cast<float4*>(step_records(s));
   a.turn_limit = s.turn_limit;
   return a;
 }

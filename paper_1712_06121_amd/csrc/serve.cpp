@@ -59,6 +59,7 @@ int server_fail(cube_server* s, const Error& e) {
 
 void enqueue_slice(cube_server& srv, Job& j) {
   cube::Sim& s = j.sim->s;
+  cube::job_records(s);
   (void)cube::enqueue_steps(s, srv.slice);
   CUBE_HIP(hipEventRecord(j.done, j.stream));
 }
@@ -66,6 +67,7 @@ void enqueue_slice(cube_server& srv, Job& j) {
 // a finished or failed job keeps its stream (its simulation still uses it) until released
 void retire(cube_server& srv, Job& j, int state) {
   j.state = state;
+  if (j.sim) cube::release_job_records(j.sim->s);
   srv.free_events.push_back(j.done);
   j.done = nullptr;
 }
@@ -86,10 +88,7 @@ void admit(cube_server& srv, Job& j) {
   srv.in_use += j.footprint;
   j.state = ACTIVE;
   int rc = cube_create(&j.p, j.stream, srv.has_alloc ? &srv.alloc : nullptr, &j.sim);
-  if (rc == CUBE_OK) {
-    j.sim->s.rec_in_footprint = true;  // admission counts footprints
-    rc = cube_init_ic(j.sim);
-  }
+  if (rc == CUBE_OK) rc = cube_init_ic(j.sim);
   if (rc != CUBE_OK) {
     j.rc = rc;
     j.error = j.sim ? cube_last_error(j.sim) : cube_last_error(nullptr);
