@@ -7,6 +7,7 @@
 #include <new>
 
 #include "cube_internal.h"
+#include "device_guard.h"
 
 namespace {
 thread_local std::string g_create_error;  // text of the last failed cube_create on this thread
@@ -21,6 +22,7 @@ void* Sim::dmalloc(size_t bytes) {
     p = alloc.alloc(bytes, alloc.user);
     if (!p) throw Error{CUBE_E_NOMEM, "device allocator returned NULL for " + std::to_string(bytes) + " bytes"};
   } else {
+    DeviceGuard on(device);
     if (hipMalloc(&p, bytes) != hipSuccess) {
       (void)hipGetLastError();
       throw Error{CUBE_E_NOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed"};
@@ -82,6 +84,7 @@ StepRecords::StepRecords(const std::vector<Sim*>& boxes, int64_t steps, hipStrea
     return;
   }
   if (need > ((size_t)1 << 30)) {
+    DeviceGuard on(owner.device);
     size_t avail = 0, total = 0;
     if (hipMemGetInfo(&avail, &total) != hipSuccess) {
       (void)hipGetLastError();
