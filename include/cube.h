@@ -339,7 +339,8 @@ typedef struct {
                               width dividing fft_col_width (default: fft_col_width) */
 } cube_variant;
 /* Time the variants on the current state (deposits, solves, then moves whose result is
- * discarded) and keep the fastest of each stage. The particle state is unchanged; the mesh
+ * discarded) and keep the fastest of each stage (move_variant, without effect on steps with records, is
+ * timed where there are none and -1 else). The particle state is unchanged; the mesh
  * afterwards holds the potential of the current state. Errors: CUBE_E_STATE (no particles). */
 int cube_autotune(cube_sim* sim);
 /* The times the last cube_autotune measured, one "stage variant t ms;" item per timed variant

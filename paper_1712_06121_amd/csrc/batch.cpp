@@ -262,7 +262,9 @@ void autotune_sim(Sim& s) {
   note("count", tc);
   for (int v = 0; v < tried; ++v) note("scatter " + std::to_string(v), ts[v]);
   s.autotune_report = rep;
-  s.move_variant = tried == 2 && ts[1] < ts[0] ? 2 : 0;
+  // not timed: by density, for steps that have to do without records (2048^3 particles: per-corner gradient
+  // 166 ms, gradient tile 128)
+  s.move_variant = tried == 1 ? -1 : (ts[1] < ts[0] ? 2 : 0);
   // a timed move may have raised a flag that the real step will raise again; clear it here
   CUBE_HIP(hipMemsetAsync(s.flags, 0, sizeof(uint32_t), s.stream));
   CUBE_HIP(hipStreamSynchronize(s.stream));

@@ -197,3 +197,24 @@ def test_a_job_keeps_within_its_footprint(lib, memory, alone):
             sim.init_ic()
             sim.step(BASE["n_steps"])
             same(got, sim.get_state(), f"job {i}")
+
+
+@pytest.mark.parametrize("i", [0, 2])
+def test_autotune_chooses_the_scatter_for_steps_without_records(lib, memory, alone, i):
+    with lib.Sim(**BOXES[i]) as sim:
+        sim.init_ic()
+        sim.autotune()
+        assert sim.variant["move_variant"] == -1  # not timed: by density
+        created = memory.total
+        memory.limit = created
+        sim.step(12)
+        memory.limit = None
+        same(sim.get_state(), alone[i], "chosen by density")
+    with lib.Sim(**BOXES[i]) as sim:
+        sim.init_ic()
+        memory.limit = memory.total
+        sim.autotune()
+        assert sim.variant["move_variant"] in (0, 2)  # timed
+        sim.step(12)
+        memory.limit = None
+        same(sim.get_state(), alone[i], "timed")
