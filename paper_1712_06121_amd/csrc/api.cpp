@@ -593,7 +593,6 @@ int cube_create(const cube_params* params, void* stream, const cube_allocator* a
     CUBE_HIP(hipMemsetAsync(s.mesh, 0, s.mesh_plan.field_floats() * sizeof(float), s.stream));
     CUBE_HIP(hipStreamSynchronize(s.stream));
     for (auto& e : s.ev) CUBE_HIP(hipEventCreate(&e));
-    s.a_now = p.a_init;
   } catch (const Error& e) {
     g_create_error = e.msg;
     cube_destroy(sim);

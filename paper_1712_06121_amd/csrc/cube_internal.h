@@ -178,10 +178,9 @@ struct Sim {
   int* step_dev = nullptr;     // step index and records read by graph-replayed move kernels (a StepWord, device)
   int steps_done = 0;
   bool half_drift_done = false;
-  int move_variant = 0;     // move passes: -1 by particle density, 0 per-corner gradient, 1 gradient tile
+  int move_variant = 0;     // scatter without records: -1 by particle density, 0, 3 per-corner gradient, 1, 2 gradient tile
   int deposit_variant = 3;  // as set (0 .. 3), without effect
   std::string autotune_report;  // per-variant times of the last cube_autotune
-  double a_now = 0.0;
   bool have_particles = false;
 
   // phases (the initial half drift, steps) enqueued since the flags were last checked, with the
@@ -322,7 +321,6 @@ void launch_unpack_codes(Sim& s, hipStream_t st);
 void launch_pack_codes(Sim& s, hipStream_t st);
 // particle IDs 0 .. n-1 in storage order (when IDs are enabled)
 void launch_pid_iota(Sim& s, hipStream_t st);
-void launch_power_finish(Sim& s, int nbins, double* k, double* pk, double* nmodes);
 // device address of the allocation-free entry point's fixed shell-sum array on device `dev`
 // (looked up once per device; noalloc.hip)
 double* noalloc_scratch(int dev);

@@ -41,8 +41,6 @@ constexpr int F = 4 * T;        // fine cells per tile side
 constexpr int PH = F + 6;       // potential tile side (3-cell halo)
 constexpr int RG = T + 2;       // new-cell region side (tile + ring)
 constexpr int RC = RG * RG * RG;
-constexpr int SRC = RC;         // deposit source cells (tile + ring)
-constexpr int BLK = 256;
 constexpr int LINK_BLK = 256;
 
 template <int NCHI>
@@ -1328,7 +1326,8 @@ __global__ __launch_bounds__(CNTH) __attribute__((amdgpu_waves_per_eu(8))) void 
 
 // Eq. (nu): the codes nu with ext[nu + h] <= u < ext[nu + h + 1] (h = (M-1)/2; ext is the edge table with
 // -inf and +inf at its ends). x = (M / pi) atan(u) in FP32 (atan z = z P(z^2) on [0, 1], eight
-// coefficients fitted to 4e-8; M / 2 - x(1 / u) beyond) is off by at most 2e-5 codes for M = 255 and 0.005
+// coefficients of a near-minimax fit: its error alternates over nine extrema of 2.7e-8 to 4.8e-8;
+// M / 2 - x(1 / u) beyond) is off by at most 2e-5 codes for M = 255 and 0.005
 // for M = 65535 (over every edge, its neighbours and 2e7 other floats, the reciprocal up to an ulp off). So
 // the nearest integer is the code unless x lies close to the middle of two, where the table decides:
 // 0.02 and 2.4 in a hundred. Against a bucket table, whose entry two exact steps then corrected (five
@@ -1472,8 +1471,8 @@ __device__ __forceinline__ void scatter_dense_tile(MoveArgs a, const unsigned lb
   resolve_factors(a);
   constexpr int NTH = 1024;
   constexpr int SH = 8 * NCHI - 1;
-  // one region holds the potential tile, then the gradient tile computed from it: with the
-  // moments added to the global accumulators directly, two workgroups fit a CU
+  // one region holds the potential tile, then the gradient tile computed from it, so that two
+  // workgroups fit a CU
   constexpr int NG = 3 * DG * DG * DG;
   static_assert(PH * PH * PH <= NG, "the potential tile must fit the gradient region");
   __shared__ float tile[NG];
