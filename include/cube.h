@@ -74,7 +74,9 @@ typedef struct {
 } cube_params;
 
 /* Optional device allocator (e.g. a framework's caching allocator). alloc returns a device
- * pointer of at least `bytes` bytes aligned to 256 bytes, or NULL; free releases it. */
+ * pointer of at least `bytes` bytes aligned to 256 bytes, or NULL; free releases it. The memory may still
+ * be in use by work enqueued before on the stream that the simulation or batch was created with (a
+ * server: the null stream); memory that is freed is not in use any more. */
 typedef struct {
   void* (*alloc)(size_t bytes, void* user);
   void (*free)(void* ptr, void* user);

@@ -31,6 +31,7 @@ void* Sim::dmalloc(size_t bytes) {
   dev_bytes += (int64_t)bytes;
   owned.push_back(p);
   sizes.push_back(bytes);
+  order_behind_allocator(*this);
   return p;
 }
 
@@ -102,6 +103,12 @@ StepRecords::StepRecords(const std::vector<Sim*>& boxes, int64_t steps, hipStrea
     if (e.code != CUBE_E_NOMEM) throw;
     return;
   }
+  try {
+    for (size_t i = 1; i < boxes_.size(); ++i) order_behind_allocator(*boxes_[i]);  // dmalloc: the owner
+  } catch (...) {
+    owner.dfree(block_);
+    throw;
+  }
   char* at = static_cast<char*>(block_);
   for (Sim* s : boxes_) {
     s->rec = at;
@@ -127,6 +134,14 @@ void job_records(Sim& s) {
   } catch (const Error& e) {
     if (e.code != CUBE_E_NOMEM) throw;
   }
+}
+
+void order_behind_allocator(Sim& s) {
+  if (!s.has_alloc || s.alloc_stream == s.stream || !s.ev[13]) return;  // (no events yet: cube_create)
+  if (hipStreamQuery(s.alloc_stream) == hipSuccess) return;  // nothing pending: the usual case, 10 us a box cheaper
+  (void)hipGetLastError();
+  CUBE_HIP(hipEventRecord(s.ev[13], s.alloc_stream));
+  CUBE_HIP(hipStreamWaitEvent(s.stream, s.ev[13], 0));
 }
 
 void release_job_records(Sim& s) {
@@ -516,6 +531,7 @@ int cube_create(const cube_params* params, void* stream, const cube_allocator* a
   try {
     s.p = *params;
     s.stream = static_cast<hipStream_t>(stream);
+    s.alloc_stream = s.stream;
     CUBE_HIP(hipGetDevice(&s.device));
     (void)cube::noalloc_scratch(s.device);  // set-up of the allocation-free entry point, once per device
     if (alloc && alloc->alloc && alloc->free) {

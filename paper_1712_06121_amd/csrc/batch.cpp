@@ -354,6 +354,8 @@ int cube_batch_create(const cube_params* params, int32_t nbox, void* stream, con
       CUBE_HIP(hipStreamCreateWithFlags(&b->main, hipStreamNonBlocking));
       b->own_main = true;
     }
+    // the boxes are set up on streams of their own, in memory that work on the given one may still use
+    if (alloc && alloc->alloc && alloc->free) CUBE_HIP(hipStreamSynchronize(static_cast<hipStream_t>(stream)));
     for (int i = 1; i < nbox; ++i)
       if (params[i].n_steps != params[0].n_steps) throw Error{CUBE_E_INVALID, "every box must have the same n_steps"};
     CUBE_HIP(hipEventCreateWithFlags(&b->fork, hipEventDisableTiming));
@@ -367,6 +369,7 @@ int cube_batch_create(const cube_params* params, int32_t nbox, void* stream, con
       cube_sim* sim = nullptr;
       const int rc = cube_create(&params[i], st, alloc, &sim);
       if (rc != CUBE_OK) throw Error{rc, "box " + std::to_string(i) + ": " + cube_last_error(nullptr)};
+      sim->s.alloc_stream = static_cast<hipStream_t>(stream);
       b->boxes.push_back(sim);
     }
   } catch (const Error& e) {

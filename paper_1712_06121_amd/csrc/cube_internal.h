@@ -111,6 +111,9 @@ struct Sim {
   int device = 0;  // the HIP device the simulation was created on
   cube_allocator alloc{};
   bool has_alloc = false;
+  // the stream behind whose work the allocator's memory is free: the simulation's own, or for boxes of a
+  // batch and jobs of a server, which run on streams of their own, the one their creator was given
+  hipStream_t alloc_stream = nullptr;
   std::string last_error;
 
   int nm = 0, nc = 0, np = 0, nchi = 1, nnu = 1;
@@ -207,7 +210,7 @@ struct Sim {
 
   // profiling: per-kernel event pairs recorded on the simulation's stream
   bool profiling = false;
-  hipEvent_t ev[16] = {};
+  hipEvent_t ev[16] = {};  // 0 .. 11, 14, 15: timings; 13: order_behind_allocator
   double timings[16] = {};
   int timing_calls = 0;
 
@@ -247,6 +250,9 @@ class StepRecords {
 // job's footprint (its initial-condition fields are gone by then).
 void job_records(Sim& s);
 void release_job_records(Sim& s);
+// A caching allocator hands out memory that work enqueued on its stream may still use (the tensor it was
+// has been dropped, the kernels on it have not run): the simulation's stream goes behind that work.
+void order_behind_allocator(Sim& s);
 // where the step kernels write records; null: the scatter recomputes the move
 inline char* step_records(const Sim& s) { return s.turn_limit == kTurnLimit ? s.rec : nullptr; }
 // what captured move kernels read on the device, uploaded once a call

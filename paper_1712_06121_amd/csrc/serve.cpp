@@ -87,8 +87,15 @@ void admit(cube_server& srv, Job& j) {
   }
   srv.in_use += j.footprint;
   j.state = ACTIVE;
+  if (srv.has_alloc) {  // the job is set up in memory that work on the null stream may still use
+    CUBE_HIP(hipEventRecord(j.done, nullptr));
+    CUBE_HIP(hipStreamWaitEvent(j.stream, j.done, 0));
+  }
   int rc = cube_create(&j.p, j.stream, srv.has_alloc ? &srv.alloc : nullptr, &j.sim);
-  if (rc == CUBE_OK) rc = cube_init_ic(j.sim);
+  if (rc == CUBE_OK) {
+    j.sim->s.alloc_stream = nullptr;
+    rc = cube_init_ic(j.sim);
+  }
   if (rc != CUBE_OK) {
     j.rc = rc;
     j.error = j.sim ? cube_last_error(j.sim) : cube_last_error(nullptr);

@@ -218,3 +218,27 @@ def test_autotune_chooses_the_scatter_for_steps_without_records(lib, memory, alo
         sim.step(12)
         memory.limit = None
         same(sim.get_state(), alone[i], "timed")
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_records_wait_for_the_work_that_still_uses_their_memory(lib, alone, mode):
+    """PyTorch's allocator hands out the memory of a tensor that has been dropped before the kernels on it
+    have run; a batch steps on streams of its own and has to go behind them."""
+    import torch
+    a = torch.randn(6144, 6144, device="cuda")
+    need = sum((record_bytes(c) + 255) // 256 * 256 for c in BOXES)
+    with lib.Batch(BOXES) as b:
+        b.set_mode(mode)
+        b.init_ic()
+        for _ in range(4):
+            torch.cuda.synchronize()
+            x = torch.empty(need // 4, dtype=torch.int32, device="cuda")
+            for _ in range(12):  # some tens of milliseconds before the fill
+                c = a @ a
+            x.fill_(-1)
+            x.add_(c[0, 0].to(torch.int32) * 0)
+            del x, c
+            b.step(3)
+        got = [box.get_state() for box in b.boxes]
+    for i, state in enumerate(got):
+        same(state, alone[i], f"box {i}")
